@@ -259,8 +259,27 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
     if (tid == 0) mupart[L] = mus - muc;
 }
 
-// Sums the frame groups (compensated) and divides by F; mirrors the power
-// spectrum rows N/2+1..N-1 from P(-u) = P(u).
+// The passes over a patch's frame-group partials (below) give every entry of
+// the stored half plane (rows 0..N/2) a thread of its own, FIN_PARTS
+// workgroups per patch: each thread waits for its few dependent sums once, and
+// even one patch spreads over several CUs.  (One workgroup per patch walked
+// the whole plane in a chain of 64 waits: 74 us for 12 patches of 6 groups, 5 now;
+// 194 us for 1287 patches of 5 groups, 104 now.)  The
+// half plane's entry also writes its mirror, P(-u) = P(u).
+template <int N> struct FinGeom {
+    static constexpr int NP = (N / 2 + 1) * N;               // stored entries
+    static constexpr int PARTS = (NP + NT - 1) / NT;         // workgroups per patch
+};
+
+// Index of -u for entry j of the half plane, or -1 where no row above N/2
+// mirrors it (rows 0 and N/2 hold both of their halves).
+template <int N>
+__device__ __forceinline__ int mirror_of(int j) {
+    const int uy = j / N, ux = j % N;
+    return uy >= 1 && uy < N / 2 ? (N - uy) * N + ((N - ux) & (N - 1)) : -1;
+}
+
+// Sums the frame groups (compensated) and divides by F.
 template <int N>
 __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int chunk_frames,
                                                      const float *__restrict__ ppart,
@@ -268,21 +287,26 @@ __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int ch
                                                      const float *__restrict__ mupart,
                                                      float *__restrict__ power, float *__restrict__ mean_spec,
                                                      float *__restrict__ mu) {
-    constexpr int HALF = N / 2, NP = (HALF + 1) * N;
-    const int patch = blockIdx.x;
+    constexpr int NP = FinGeom<N>::NP;
+    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
     const int b = burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; });
     const BurstDesc &bd = bt.b[b];
     const int nchunks = (bd.F + chunk_frames - 1) / chunk_frames;
     const float invF = 1.0f / (float)bd.F;
     const size_t wg0 = (size_t)bd.ingest0 + (size_t)(patch - bd.patch0) * nchunks;   // its first ingest workgroup
-    const float *pp = ppart + wg0 * NP;
-    for (int j = threadIdx.x; j < N * N; j += NT) {
-        const int uy = j / N, ux = j % N;
-        const int src = uy <= HALF ? j : ((N - uy) * N + ((N - ux) & (N - 1)));
+    const int j = part * NT + threadIdx.x;
+    if (j < NP) {
+        const float *pp = ppart + wg0 * NP + j;
         float s = 0.f, c = 0.f;
-        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, pp[(size_t)k * NP + src]);
-        power[(size_t)patch * N * N + j] = (s - c) * invF;
+#pragma unroll 8
+        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, pp[(size_t)k * NP]);
+        const float v = (s - c) * invF;
+        float *pw = power + (size_t)patch * N * N;
+        pw[j] = v;
+        const int m = mirror_of<N>(j);
+        if (m >= 0) pw[m] = v;
     }
+    if (part != 0) return;
     if (threadIdx.x < 4) {
         float s = 0.f, c = 0.f;
         for (int k = 0; k < nchunks; ++k) kahan_add(s, c, mpart[(wg0 + k) * 4 + threadIdx.x]);
@@ -308,15 +332,25 @@ __global__ __launch_bounds__(NT) void k_acc_stream(int nchunks, const float *__r
                                                    int last,
                                                    float inv_total, float *__restrict__ power,
                                                    float *__restrict__ mean_spec, float *__restrict__ mu) {
-    constexpr int HALF = N / 2, NP = (HALF + 1) * N;
-    const int patch = blockIdx.x;
-    const float *pp = ppart + (size_t)patch * nchunks * NP;
-    float2 *ps = psc + (size_t)patch * NP;
-    for (int j = threadIdx.x; j < NP; j += NT) {
-        float2 v = first ? make_float2(0.f, 0.f) : ps[j];
-        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, pp[(size_t)k * NP + j]);
-        ps[j] = v;
+    constexpr int NP = FinGeom<N>::NP;
+    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
+    const int j = part * NT + threadIdx.x;
+    if (j < NP) {
+        const float *pp = ppart + (size_t)patch * nchunks * NP + j;
+        float2 *ps = psc + (size_t)patch * NP + j;
+        float2 v = first ? make_float2(0.f, 0.f) : *ps;
+#pragma unroll 8
+        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, pp[(size_t)k * NP]);
+        *ps = v;
+        if (last) {
+            float *pw = power + (size_t)patch * N * N;
+            const float m = (v.x - v.y) * inv_total;
+            pw[j] = m;
+            const int mj = mirror_of<N>(j);
+            if (mj >= 0) pw[mj] = m;
+        }
     }
+    if (part != 0) return;
     if (threadIdx.x < 4) {
         float2 v = first ? make_float2(0.f, 0.f) : msc[(size_t)patch * 4 + threadIdx.x];
         for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, mpart[((size_t)patch * nchunks + k) * 4 + threadIdx.x]);
@@ -328,14 +362,6 @@ __global__ __launch_bounds__(NT) void k_acc_stream(int nchunks, const float *__r
         for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, mupart[(size_t)patch * nchunks + k]);
         musc[patch] = v;
         if (last) mu[patch] = (v.x - v.y) * inv_total;
-    }
-    if (!last) return;
-    __syncthreads();
-    for (int j = threadIdx.x; j < N * N; j += NT) {
-        const int uy = j / N, ux = j % N;
-        const int src = uy <= HALF ? j : ((N - uy) * N + ((N - ux) & (N - 1)));
-        const float2 v = ps[src];
-        power[(size_t)patch * N * N + j] = (v.x - v.y) * inv_total;
     }
 }
 
@@ -352,11 +378,11 @@ hipError_t launch_ingest_t(const IngestArgs &a, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.stream_mode == 0) {
-        hipLaunchKernelGGL((k_acc_finalize<N>), dim3(a.bt.patches), dim3(NT), 0, st, a.bt, a.chunk_frames,
+        hipLaunchKernelGGL((k_acc_finalize<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames,
                            a.ppart, a.mpart, a.mupart, a.power, a.mean_spec, a.mu);
     } else {
         const int nchunks = (a.bt.b[0].F + a.chunk_frames - 1) / a.chunk_frames;
-        hipLaunchKernelGGL((k_acc_stream<N>), dim3(a.bt.patches), dim3(NT), 0, st, nchunks, a.ppart, a.mpart,
+        hipLaunchKernelGGL((k_acc_stream<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, nchunks, a.ppart, a.mpart,
                            a.mupart, a.psc, a.msc, a.musc, a.stream_first, a.stream_mode == 2 ? 1 : 0, a.inv_total,
                            a.power,
                            a.mean_spec, a.mu);
@@ -508,15 +534,26 @@ __global__ __launch_bounds__(FT) void k_noise(const BurstTable bt, int stride, i
 // Sums the frame groups of k_noise per patch (compensated), divides by F,
 // writes C in the record layout of the spectra (rows -16 .. N/2-1, the rows
 // below 0 as C(u) = conj C(-u)), and subtracts q0 from the patch's power
-// spectrum.
+// spectrum.  One thread per stored entry, as in k_acc_finalize.
+template <int N>
+__device__ __forceinline__ void noise_store(int j, float mx, float my, float q0, float2 *cg, float *pw) {
+    constexpr int HALF = N / 2;
+    const int y = j / N, x = j % N;
+    if (y < HALF) cg[(y + SPEC_NEG_ROWS) * N + x] = make_float2(mx, my);
+    if (y >= 1 && y <= SPEC_NEG_ROWS) cg[(SPEC_NEG_ROWS - y) * N + ((N - x) & (N - 1))] = make_float2(mx, -my);
+    pw[j] -= q0;
+    const int m = mirror_of<N>(j);
+    if (m >= 0) pw[m] -= q0;
+}
+
 template <int N>
 __global__ __launch_bounds__(NT) void k_noise_finalize(const BurstTable bt, int chunk_frames,
                                                        const float2 *__restrict__ cpart,
                                                        const float *__restrict__ spart, float *__restrict__ power,
                                                        float2 *__restrict__ cgrid, float *__restrict__ nbar) {
-    constexpr int HALF = N / 2, NP = (HALF + 1) * N;
+    constexpr int NP = FinGeom<N>::NP;
     constexpr int FS = SpecRows<N>::FS;
-    const int patch = blockIdx.x;
+    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
     const int b = burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; });
     const BurstDesc &bd = bt.b[b];
     const int nchunks = (bd.F + chunk_frames - 1) / chunk_frames;
@@ -530,33 +567,27 @@ __global__ __launch_bounds__(NT) void k_noise_finalize(const BurstTable bt, int 
     }
     q0 = (q0 - q0c) * invF;
     t3 = (t3 - t3c) * invF;
-    if (threadIdx.x == 0) {
+    if (part == 0 && threadIdx.x == 0) {
         nbar[(size_t)patch * 2] = q0;
         nbar[(size_t)patch * 2 + 1] = t3;
     }
-    const float2 *cp = cpart + wg0 * NP;
-    for (int i = threadIdx.x; i < FS; i += NT) {
-        const int y = i / N - SPEC_NEG_ROWS, x = i % N;
-        const bool mirror = y < 0;
-        const int j = mirror ? (-y) * N + ((N - x) & (N - 1)) : y * N + x;
-        float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
-        for (int k = 0; k < nchunks; ++k) {
-            const float2 v = cp[(size_t)k * NP + j];
-            kahan_add(sx, cx, v.x);
-            kahan_add(sy, cy, v.y);
-        }
-        const float im = (sy - cy) * invF;
-        cgrid[(size_t)patch * FS + i] = make_float2((sx - cx) * invF, mirror ? -im : im);
+    const int j = part * NT + threadIdx.x;
+    if (j >= NP) return;
+    const float2 *cp = cpart + wg0 * NP + j;
+    float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
+#pragma unroll 8
+    for (int k = 0; k < nchunks; ++k) {
+        const float2 v = cp[(size_t)k * NP];
+        kahan_add(sx, cx, v.x);
+        kahan_add(sy, cy, v.y);
     }
-    float *pw = power + (size_t)patch * N * N;
-    for (int j = threadIdx.x; j < N * N; j += NT) pw[j] -= q0;
+    noise_store<N>(j, (sx - cx) * invF, (sy - cy) * invF, q0, cgrid + (size_t)patch * FS, power + (size_t)patch * N * N);
 }
 
-// The streaming form of k_noise_finalize: one workgroup per patch adds the
-// group's sums (its frame chunks in order, compensated) to the running
-// pairs; the last group writes the means as k_noise_finalize does.  With
-// one group holding every frame the means are those of k_noise_finalize bit
-// for bit.
+// The streaming form of k_noise_finalize: adds the group's sums (its frame
+// chunks in order, compensated) to the running pairs; the last group writes
+// the means as k_noise_finalize does.  With one group holding every frame
+// the means are those of k_noise_finalize bit for bit.
 template <int N>
 __global__ __launch_bounds__(NT) void k_noise_stream(const BurstTable bt, int chunk_frames,
                                                      const float2 *__restrict__ cpart,
@@ -564,64 +595,57 @@ __global__ __launch_bounds__(NT) void k_noise_stream(const BurstTable bt, int ch
                                                      float inv_total, float4 *__restrict__ csc,
                                                      float *__restrict__ ssc, float *__restrict__ power,
                                                      float2 *__restrict__ cgrid, float *__restrict__ nbar) {
-    constexpr int HALF = N / 2, NP = (HALF + 1) * N;
+    constexpr int NP = FinGeom<N>::NP;
     constexpr int FS = SpecRows<N>::FS;
-    const int patch = blockIdx.x;
+    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
     const BurstDesc &bd = bt.b[0];
     const int nchunks = (bd.F + chunk_frames - 1) / chunk_frames;
     const size_t wg0 = (size_t)bd.ingest0 + (size_t)patch * nchunks;
-    // every thread forms the same two sums in the same order
-    float q0 = 0.f, q0c = 0.f, t3 = 0.f, t3c = 0.f;
-    float *sp = ssc + (size_t)patch * 4;
-    if (!first) {
-        q0 = sp[0]; t3 = sp[1]; q0c = sp[2]; t3c = sp[3];
-    }
-    for (int k = 0; k < nchunks; ++k) {
-        kahan_add(q0, q0c, spart[(wg0 + k) * 2]);
-        kahan_add(t3, t3c, spart[(wg0 + k) * 2 + 1]);
-    }
-    __syncthreads();                              // every thread has read the running pair
-    if (mode == 1) {
-        if (threadIdx.x == 0) {
-            sp[0] = q0; sp[1] = t3; sp[2] = q0c; sp[3] = t3c;
-        }
-    } else {
-        q0 = (q0 - q0c) * inv_total;
-        t3 = (t3 - t3c) * inv_total;
-        if (threadIdx.x == 0) {
-            nbar[(size_t)patch * 2] = q0;
-            nbar[(size_t)patch * 2 + 1] = t3;
-        }
-    }
-    const float2 *cp = cpart + wg0 * NP;
-    float4 *cs = csc + (size_t)patch * NP;
-    float2 *cg = cgrid + (size_t)patch * FS;
-    for (int j = threadIdx.x; j < NP; j += NT) {
-        float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
+    // q0 and T: the patch's first workgroup alone keeps the running pairs
+    // (mode 1); in mode 2 nothing writes them, and every thread forms the
+    // same two means in the same order
+    float q0 = 0.f, t3 = 0.f;
+    if (mode != 1 || (part == 0 && threadIdx.x == 0)) {
+        float q0c = 0.f, t3c = 0.f;
+        float *sp = ssc + (size_t)patch * 4;
         if (!first) {
-            const float4 r = cs[j];
-            sx = r.x; sy = r.y; cx = r.z; cy = r.w;
+            q0 = sp[0]; t3 = sp[1]; q0c = sp[2]; t3c = sp[3];
         }
         for (int k = 0; k < nchunks; ++k) {
-            const float2 v = cp[(size_t)k * NP + j];
-            kahan_add(sx, cx, v.x);
-            kahan_add(sy, cy, v.y);
+            kahan_add(q0, q0c, spart[(wg0 + k) * 2]);
+            kahan_add(t3, t3c, spart[(wg0 + k) * 2 + 1]);
         }
         if (mode == 1) {
-            cs[j] = make_float4(sx, sy, cx, cy);
-            continue;
+            sp[0] = q0; sp[1] = t3; sp[2] = q0c; sp[3] = t3c;
+        } else {
+            q0 = (q0 - q0c) * inv_total;
+            t3 = (t3 - t3c) * inv_total;
+            if (part == 0 && threadIdx.x == 0) {
+                nbar[(size_t)patch * 2] = q0;
+                nbar[(size_t)patch * 2 + 1] = t3;
+            }
         }
-        // means at their record place (rows 0 .. N/2 - 1), and the conjugate
-        // mirrors of rows 1 .. SPEC_NEG_ROWS in rows -1 .. -SPEC_NEG_ROWS
-        const int y = j / N, x = j % N;
-        const float mx = (sx - cx) * inv_total, my = (sy - cy) * inv_total;
-        if (y < HALF) cg[(y + SPEC_NEG_ROWS) * N + x] = make_float2(mx, my);
-        if (y >= 1 && y <= SPEC_NEG_ROWS) cg[(SPEC_NEG_ROWS - y) * N + ((N - x) & (N - 1))] = make_float2(mx, -my);
     }
-    if (mode == 2) {
-        float *pw = power + (size_t)patch * N * N;
-        for (int j = threadIdx.x; j < N * N; j += NT) pw[j] -= q0;
+    const int j = part * NT + threadIdx.x;
+    if (j >= NP) return;
+    const float2 *cp = cpart + wg0 * NP + j;
+    float4 *cs = csc + (size_t)patch * NP + j;
+    float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
+    if (!first) {
+        const float4 r = *cs;
+        sx = r.x; sy = r.y; cx = r.z; cy = r.w;
     }
+#pragma unroll 8
+    for (int k = 0; k < nchunks; ++k) {
+        const float2 v = cp[(size_t)k * NP];
+        kahan_add(sx, cx, v.x);
+        kahan_add(sy, cy, v.y);
+    }
+    if (mode == 1)
+        *cs = make_float4(sx, sy, cx, cy);
+    else
+        noise_store<N>(j, (sx - cx) * inv_total, (sy - cy) * inv_total, q0, cgrid + (size_t)patch * FS,
+                       power + (size_t)patch * N * N);
 }
 
 template <int N, typename T>
@@ -638,10 +662,10 @@ hipError_t launch_noise_t(const NoiseArgs &na, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.stream_mode == 0)
-        hipLaunchKernelGGL((k_noise_finalize<N>), dim3(a.bt.patches), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
+        hipLaunchKernelGGL((k_noise_finalize<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
                            na.spart, a.power, na.cgrid, na.nbar);
     else
-        hipLaunchKernelGGL((k_noise_stream<N>), dim3(a.bt.patches), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
+        hipLaunchKernelGGL((k_noise_stream<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
                            na.spart, a.stream_mode, a.stream_first, a.inv_total, na.csc, na.ssc, a.power, na.cgrid,
                            na.nbar);
     return hipGetLastError();
