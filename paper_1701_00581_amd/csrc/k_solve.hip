@@ -69,6 +69,20 @@ __device__ __forceinline__ double wave_total_lane63(double v) {
     return v;
 }
 
+// Sums of x and of y over each half wave: the rows of 16 lanes get, in turn,
+// the first half's x and y and the second half's x and y (x's and y's rows
+// exchanged first, so that both sums run as one).
+__device__ __forceinline__ double half_wave_totals(double x, double y) {
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    double v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    v += dpp_d<0xb1>(v);     // quad_perm [1,0,3,2]
+    v += dpp_d<0x4e>(v);     // quad_perm [2,3,0,1]
+    v += dpp_d<0x141>(v);    // row_half_mirror
+    v += dpp_d<0x140>(v);    // row_mirror: every lane holds its row's sum
+    return v;
+}
+
 // Samples of one unit for this lane: lane l takes samples l, l + 64, ...
 // of the wave's w (w and bar are wave-uniform).
 template <int TPL>
@@ -79,7 +93,7 @@ struct UnitRegs {
 };
 
 template <int N, int TPL, int BIG>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6 : 2))) void k_solve(int nW, int n_units, const int *__restrict__ units,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6 : 2))) void k_solve(int base, int nW, int n_units, const int *__restrict__ units,
                                               int zero_slot, const unsigned *__restrict__ code,
                                               const int *__restrict__ Wxy, const float *__restrict__ power,
                                               const float *__restrict__ mean_spec,
@@ -88,7 +102,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6
                                               double *__restrict__ amp, double2 *__restrict__ phasor) {
     __shared__ double2 e[Win<BIG>::INNER + Win<BIG>::RING + 1];   // + the zero phasor
     __shared__ double red[NWAVE];
-    const int patch = blockIdx.x;
+    const int patch = base + blockIdx.x;
     const double *stf = bt.b[burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; })].stf;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -247,6 +261,310 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6
             if (u < n_units) {
                 solve(buf[d]);
                 if (buf[d].bar) __syncthreads();
+            }
+        }
+    }
+}
+
+// The modulus and phase of one patch per workgroup, in steps, for bursts of
+// few patches (see PHASE_MAX_PATCHES) and v radii of at most PH_MAX_PAIRS
+// pairs +-v (R <= 12); k_solve takes the others.
+//
+// The recursion is a chain of about 960 dependent groups of shells per patch
+// (N = 128), and k_solve pays for every link the whole of a unit's work: the
+// loads, two scattered LDS gathers per sample, the 64-lane sums and the
+// root, 0.8 us a link.  But of a w's up to 214 samples only a few (8 at most,
+// 2.6 on average) read a phasor of the two steps before.  So the waves have
+// roles:
+//   bulk waves (two w of the next step each, one per half wave) sum the
+//     bulk of step s + 1, from phasors gathered during the step before, and
+//     gather those of step s + 2;
+//   the critical wave (8 lanes per w, one fresh sample each) meanwhile adds
+//     the fresh samples of step s to the bulk sums the step before left in
+//     LDS, takes the root and writes the phasors.
+// A step then costs one short LDS - sum - root - LDS chain and one barrier.
+// A bulk lane keeps the phasors of its pairs +-v (a w has at most one of each
+// pair, the one on its side of the origin) in registers, so a sample costs
+// one LDS gather, on a raster of the plane where neighbouring lanes read
+// neighbouring entries.  Codes are loaded RING - 1 steps ahead and the samples
+// they place AHEAD steps ahead.
+// A step takes 0.49 us: the bulk waves issue for 1130 of its 1190 clocks (a
+// vector load holds its wave for about 43 clocks, an LDS gather for 24, a
+// sample's arithmetic for 77), the critical wave for 650.  Fewer, wider
+// loads and one sample's loads between the next samples' arithmetic took it
+// from 0.57; the memory's latency is not in it (the same with every load from
+// one 4 KB window).
+// The raster (154 KB at N = 128, R = 12) allows one workgroup per CU there,
+// whose 8 waves then have 256 registers each.
+// n consecutive words at byte offset off of r (n 1..4)
+template <int n>
+__device__ __forceinline__ void load_words(const __amdgpu_buffer_rsrc_t r, unsigned off, unsigned *w) {
+    if constexpr (n == 1) w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+    if constexpr (n == 2) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+        w[0] = v[0]; w[1] = v[1];
+    }
+    if constexpr (n == 3) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b96(r, (int)off, 0, 0);
+        w[0] = v[0]; w[1] = v[1]; w[2] = v[2];
+    }
+    if constexpr (n == 4) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+        w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
+    }
+}
+
+constexpr int PH_NT = 512;                   // the waves past the bulk waves end before the recursion
+static_assert(1 + PH_BULK <= PH_NT / 64 && PH_WIDE * PH_FRESH == 64, "lanes of the critical wave");
+template <int N> constexpr int ph_entries_max() { return (N / 2 + 12) * (N - 1) + 1; }   // u_cut < N/2, R <= 12
+
+struct PhaseArgs {
+    int steps, early, entries, s_count;
+    const unsigned *code, *step;
+    const uint4 *crit;
+    const int *vslot;
+};
+
+template <int N, int TPL>
+__global__ __launch_bounds__(PH_NT) __attribute__((amdgpu_waves_per_eu(N == 128 ? 2 : TPL <= 4 ? 4 : 2))) void k_phase(
+    int base, int nW, const PhaseArgs pa, const int *__restrict__ Wxy, const float *__restrict__ power,
+    const float *__restrict__ mean_spec, const float2 *__restrict__ bispec, const BurstTable bt, double floor_,
+    int noise_bias, double *__restrict__ amp, double2 *__restrict__ phasor) {
+    constexpr int PWAVES = PH_NT / 64;
+    constexpr int RING = 8, AHEAD = 3, BUF = 4;
+    static_assert(RING % BUF == 0 && AHEAD < BUF, "a sample buffer is free before it is loaded");
+    __shared__ double2 e[ph_entries_max<N>()];
+    __shared__ double zb[2][PH_WIDE][2];         // bulk sums of the step to be finished
+    __shared__ double red[2][PWAVES];
+    const int patch = base + blockIdx.x;
+    const double *stf = bt.b[burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; })].stf;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const float *P = power + (size_t)patch * N * N;
+    double2 *ph_out = phasor + (size_t)patch * nW;
+
+    // entries not yet known read as 0
+    for (int i = tid; i < pa.entries; i += PH_NT) e[i] = make_double2(0.0, 0.0);
+    // noise level: mean power where |u| > N/2 + 2 (signed u in [-N/2, N/2))
+    double nb = 0.0;
+    if (noise_bias) {
+        double acc = 0.0;
+        int cnt = 0;
+        const double lim = (N / 2 + 2.0) * (N / 2 + 2.0);
+        static_assert(N * N % PH_NT == 0, "whole passes");
+        // (every value is loaded, so that the loads of the unrolled passes go out together)
+#pragma unroll 8
+        for (int j = tid; j < N * N; j += PH_NT) {
+            int ux = j % N, uy = j / N;
+            ux = ux >= N / 2 ? ux - N : ux;
+            uy = uy >= N / 2 ? uy - N : uy;
+            const double pj = (double)P[j];
+            if ((double)(ux * ux + uy * uy) > lim) { acc += pj; ++cnt; }
+        }
+        acc = wave_sum_d(acc);
+        const double c = wave_sum_d((double)cnt);
+        if (lane == 0) { red[0][wave] = acc; red[1][wave] = c; }
+        __syncthreads();
+        double tot = 0.0, ctot = 0.0;
+#pragma unroll
+        for (int k = 0; k < PWAVES; ++k) { tot += red[0][k]; ctot += red[1][k]; }
+        nb = tot / ctot;
+    }
+    // modulus, Eq. 1 (loads unconditional, so that unrolled passes overlap)
+#pragma unroll 4
+    for (int i = tid; i < nW; i += PH_NT) {
+        const int wx = Wxy[2 * i], wy = Wxy[2 * i + 1];
+        const int j = (wy & (N - 1)) * N + (wx & (N - 1));
+        const double s = stf[j];
+        const double num = (double)P[j] - nb;
+        double a = 0.0;
+        if (s >= floor_) a = sqrt((num > 0.0 ? num : 0.0) / s);
+        amp[(size_t)patch * nW + i] = a;
+    }
+    __syncthreads();
+    // seeds (1,0) and (0,1) are W[0] and W[1]
+    if (tid < 2) {
+        const float *m = mean_spec + (size_t)patch * 4 + 2 * tid;
+        const double2 s = unit_or_one(make_double2((double)m[0], (double)m[1]));
+        ph_out[tid] = s;
+        const uint4 c = pa.crit[tid];
+        e[c.x] = s;
+        e[c.y] = make_double2(s.x, -s.y);
+    }
+    __syncthreads();
+
+    if (wave > PH_BULK) return;                  // (a barrier counts the waves still running)
+    // the patch's samples: an offset past them reads 0
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(bispec + (size_t)patch * pa.s_count), (short)0, pa.s_count * (int)sizeof(float2), 0x00020000);
+    auto load_b = [&](unsigned off) __attribute__((always_inline)) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, 0);
+        return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+    };
+    if (wave == 0) {
+        // critical wave: lanes 8 b .. 8 b + 7 finish w number b of the step
+        __builtin_amdgcn_s_setprio(3);
+        const uint4 *cp = pa.crit + lane;
+        uint4 c[RING];
+        float2 b[RING];
+        // (past the last step: its records again, never used)
+        auto load_c = [&](int s, int d) __attribute__((always_inline)) { c[d] = cp[(size_t)min(s, pa.steps - 1) * 64]; };
+        auto load_bs = [&](int d) __attribute__((always_inline)) { b[d] = load_b(c[d].y); };
+#pragma unroll
+        for (int d = 0; d < RING - 1; ++d) load_c(1 + d, d);
+#pragma unroll
+        for (int d = 0; d < AHEAD; ++d) load_bs(d);
+        double2 v = make_double2(0.0, 0.0);
+        int out = -1;                            // the step before's w, to be written to memory
+        for (int s0 = 1; s0 < pa.steps; s0 += RING) {
+#pragma unroll
+            for (int d = 0; d < RING; ++d) {
+                const int s = s0 + d;
+                if (s < pa.steps) {
+                    __syncthreads();
+                    const double2 ea = e[c[d].x & 0xffffu], eb = e[c[d].x >> 16];
+                    const double zx0 = zb[s & 1][lane >> 3][0], zy0 = zb[s & 1][lane >> 3][1];
+                    __builtin_amdgcn_sched_barrier(0);
+                    // while these are on their way: the loads ahead, and the
+                    // last step's phasors to memory
+                    load_bs((d + AHEAD) % RING);
+                    load_c(s + RING - 1, (d + RING - 1) % RING);
+                    if (out >= 0) ph_out[out] = v;
+                    __builtin_amdgcn_sched_barrier(0);
+                    const double px = fma(ea.x, eb.x, -ea.y * eb.y);
+                    const double py = fma(ea.x, eb.y, ea.y * eb.x);
+                    const double bx = (double)b[d].x, by = (double)b[d].y;
+                    // z = (px + i py) * conj(bx + i by)
+                    double zx = fma(px, bx, py * by);
+                    double zy = fma(py, bx, -px * by);
+                    zx += dpp_d<0xb1>(zx);       // quad_perm [1,0,3,2]
+                    zy += dpp_d<0xb1>(zy);
+                    zx += dpp_d<0x4e>(zx);       // quad_perm [2,3,0,1]
+                    zy += dpp_d<0x4e>(zy);
+                    zx += dpp_d<0x141>(zx);      // row_half_mirror: all 8 lanes hold the sum
+                    zy += dpp_d<0x141>(zy);
+                    zx += zx0;
+                    zy += zy0;
+                    const double n = zx * zx + zy * zy;
+                    const double rn = rsqrt(n);
+                    const bool some = n > 0.0;
+                    v = make_double2(some ? zx * rn : 1.0, some ? zy * rn : 0.0);
+                    if ((int)c[d].z >= 0) e[c[d].z] = make_double2(v.x, (lane & 7) ? -v.y : v.y);
+                    out = (int)c[d].w;
+                }
+            }
+        }
+        if (out >= 0) ph_out[out] = v;
+    } else {
+        // bulk waves: w number 2 (wave - 1) + (lane / 32) of the next step
+        const int b0 = 2 * (wave - 1), slot = b0 + (lane >> 5);
+        double2 ev[TPL];
+        int vs[TPL];
+#pragma unroll
+        for (int i = 0; i < TPL; ++i) {
+            vs[i] = pa.vslot[32 * i + (lane & 31)];
+            ev[i] = make_double2(0.0, 0.0);
+        }
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)pa.code, (short)0, nW * (TPL * 128), 0x00020000);
+        const float2 *B = bispec + (size_t)patch * pa.s_count;
+        constexpr int P0 = TPL < 4 ? TPL : 4;    // codes of the first run (ph_code_at)
+        unsigned c[RING][TPL];
+        float2 b[BUF][TPL];
+        unsigned st[RING], t0[RING];             // the steps' words (wave-uniform)
+        // steps in blocks of 64, one per lane
+        const uint2 *sp = (const uint2 *)pa.step + lane;
+        uint2 cur = sp[0], nxt = sp[64];
+        // the steps' words, and the offset of this lane's codes (in the
+        // current block of steps; a half wave without a w reads past the
+        // table, i.e. zeros)
+        auto entry = [&](int s, int d) __attribute__((always_inline)) {
+            st[d] = __builtin_amdgcn_readlane(cur.x, s & 63);
+            t0[d] = __builtin_amdgcn_readlane(cur.y, s & 63);
+            const unsigned at = ((st[d] & 0x1fffu) + (unsigned)slot) * (TPL * 128u) + (unsigned)(4 * P0) * (unsigned)(lane & 31);
+            return slot < (int)((st[d] >> 13) & 15u) ? at : 0x7ffffff0u;
+        };
+        // (loads cost the address unit 16 clocks each whatever their width, so
+        // a lane's codes come in one or two)
+        auto load_c = [&](unsigned at, int d) __attribute__((always_inline)) {
+            load_words<P0>(rc, at, &c[d][0]);
+            if constexpr (TPL > P0)
+                load_words<TPL - P0>(rc, at + 128u * P0 - (unsigned)(4 * (2 * P0 - TPL)) * (unsigned)(lane & 31), &c[d][P0]);
+        };
+        // the samples of a step: a buffer of just its own, so that a pair
+        // without one reads 0
+        auto samples = [&](int d) __attribute__((always_inline)) {
+            return __builtin_amdgcn_make_buffer_rsrc((void *)(B + t0[d]), (short)0,
+                                                     (int)((st[d] >> 17) * sizeof(float2)), 0x00020000);
+        };
+        auto load_s = [&](const __amdgpu_buffer_rsrc_t rb, int i, int d) __attribute__((always_inline)) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rb, (int)((c[d][i] >> 16) & 0xfff8u), 0, 0);
+            b[d % BUF][i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+        };
+#pragma unroll
+        for (int d = 0; d < RING - 1; ++d) {
+            load_c(entry(1 + d, d), d);
+        }
+#pragma unroll
+        for (int d = 0; d < AHEAD; ++d)
+#pragma unroll
+            for (int i = 0; i < TPL; ++i) load_s(samples(d), i, d);
+        auto has = [&](int d) __attribute__((always_inline)) { return b0 < (int)((st[d] >> 13) & 15u); };
+        // the phasors of w -+ v of this and of the next step
+        double2 ga[2][TPL];
+        auto gather = [&](const unsigned (&k)[TPL], double2 (&g)[TPL]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < TPL; ++i) g[i] = *(const double2 *)((const char *)e + (k[i] & 0x3fff0u));
+        };
+        gather(c[0], ga[0]);                     // (step 1 has no bulk: all of them `zero`)
+        // set d holds step s = s0 + 1 + d; the codes read in a pass are those
+        // of steps s0 + RING .. s0 + 2 RING - 1, in one block (64 % RING == 0)
+        for (int s0 = 0; s0 + 1 < pa.steps; s0 += RING) {
+            if (((s0 + RING) & 63) == 0) {
+                cur = nxt;
+                nxt = sp[s0 + RING + 64];
+            }
+#pragma unroll
+            for (int d = 0; d < RING; ++d) {
+                const int s = s0 + 1 + d;
+                const bool on = s < pa.steps && has(d);
+                if (has((d + 1) % RING)) gather(c[(d + 1) % RING], ga[(d + 1) % 2]);
+                const int DB = (d + AHEAD) % RING, DC = (d + RING - 1) % RING;
+                const __amdgpu_buffer_rsrc_t rb = samples(DB);
+                const unsigned at = entry(s + RING - 1, DC);
+                double zx = 0.0, zy = 0.0;
+                // (the loads ahead go out between the samples)
+                load_c(at, DC);
+#pragma unroll
+                for (int i = 0; i < TPL; ++i) {
+                    if (on) {
+                        const double2 ea = ga[d % 2][i];
+                        double2 eb = ev[i];
+                        // -v: the sign bit onto the imaginary part
+                        eb.y = __longlong_as_double(__double_as_longlong(eb.y) ^
+                                                    ((long long)((c[d][i] << 13) & 0x80000000u) << 32));
+                        const double px = fma(ea.x, eb.x, -ea.y * eb.y);
+                        const double py = fma(ea.x, eb.y, ea.y * eb.x);
+                        const double bx = (double)b[d % BUF][i].x, by = (double)b[d % BUF][i].y;
+                        zx = fma(px, bx, fma(py, by, zx));
+                        zy = fma(py, bx, fma(-px, by, zy));
+                    }
+                    load_s(rb, i, DB);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (on) {
+                    const double t = half_wave_totals(zx, zy);
+                    if ((lane & 15) == 0) zb[s & 1][slot][(lane >> 4) & 1] = t;
+                }
+                // the pairs' phasors for the next step, until the last of them
+                // is known (also where this wave is idle: the last refresh is
+                // the one kept)
+                if (s <= pa.early + 2) {
+#pragma unroll
+                    for (int i = 0; i < TPL; ++i) ev[i] = e[vs[i]];
+                }
+                if (s < pa.steps) __syncthreads();
             }
         }
     }
@@ -460,14 +778,55 @@ hipError_t launch_solve_t(const SolveArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int N, int TPL>
+hipError_t launch_phase_t(const SolveArgs &a, int base, int patches, hipStream_t st) {
+    const PhaseArgs pa = {a.ph_steps, a.ph_early, a.ph_entries, (int)a.s_count,
+                          a.ph_code, a.ph_step, (const uint4 *)a.ph_crit, a.ph_vslot};
+    hipLaunchKernelGGL((k_phase<N, TPL>), dim3(patches), dim3(PH_NT), 0, st, base, a.nW, pa, a.Wxy, a.power,
+                       a.mean_spec, a.bispec, a.bt, a.floor, a.noise_bias, a.amp, a.phasor);
+    return hipGetLastError();
+}
+
+template <int N>
+hipError_t launch_phase_n(const SolveArgs &a, int base, int patches, hipStream_t st) {
+    if (a.ph_entries > ph_entries_max<N>()) return hipErrorInvalidValue;
+    switch (a.ph_tpl) {
+    case 2: return launch_phase_t<N, 2>(a, base, patches, st);
+    case 3: return launch_phase_t<N, 3>(a, base, patches, st);
+    case 4: return launch_phase_t<N, 4>(a, base, patches, st);
+    case 5: return launch_phase_t<N, 5>(a, base, patches, st);
+    case 6: return launch_phase_t<N, 6>(a, base, patches, st);
+    case 7: return launch_phase_t<N, 7>(a, base, patches, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int N, int TPL, int BIG>
+hipError_t launch_solve_t(const SolveArgs &a, int base, int patches, hipStream_t st) {
+    hipLaunchKernelGGL((k_solve<N, TPL, BIG>), dim3(patches), dim3(NT), 0, st, base, a.nW, a.n_units, a.units,
+                       a.zero_slot, a.code, a.Wxy, a.power, a.mean_spec, a.bispec,
+                       a.s_count, a.bt, a.floor, a.noise_bias, a.amp, a.phasor);
+    return hipGetLastError();
+}
+
 template <int N, int BIG>
-hipError_t launch_solve_n(const SolveArgs &a, hipStream_t st) {
+hipError_t launch_solve_n(const SolveArgs &a, int base, int patches, hipStream_t st) {
     switch (solve_samples_per_lane(a.max_sw)) {
-    case 2: return launch_solve_t<N, 2, BIG>(a, st);
-    case 4: return launch_solve_t<N, 4, BIG>(a, st);
-    default: return launch_solve_t<N, 8, BIG>(a, st);
+    case 2: return launch_solve_t<N, 2, BIG>(a, base, patches, st);
+    case 4: return launch_solve_t<N, 4, BIG>(a, base, patches, st);
+    default: return launch_solve_t<N, 8, BIG>(a, base, patches, st);
     }
 }
+
+// Bursts of at most this many patches are solved by k_phase.  k_phase holds
+// one workgroup per CU at N = 128 and k_solve three, so k_phase wins while
+// the patches fit the 256 CUs at once (ms, N = 128, R = 10: 1 patch 0.54
+// against 0.76, 225 patches 0.63 against 0.85; R = 12: 256 patches 0.75
+// against 0.87) and not in a second round (300 patches: 1.16 against 1.14 at
+// R = 10, 1.42 against 1.21 at R = 12; 1287: 4.3 against 3.8).  The two
+// round differently, so the choice goes by the burst's own patches: a burst
+// gives the same phasors alone and in a batch.
+constexpr int PHASE_MAX_PATCHES = 256;
 
 }  // namespace
 
@@ -489,8 +848,21 @@ hipError_t launch_solve(const SolveArgs &a, hipStream_t st) {
     if (a.s_count * (int64_t)sizeof(float2) > INT32_MAX) return hipErrorInvalidValue;   // buffer range of B
     const bool small = a.n_inner <= Win<0>::INNER && a.ring <= Win<0>::RING;
     if (!small && (a.n_inner > Win<1>::INNER || a.ring > Win<1>::RING)) return hipErrorInvalidValue;
-    if (a.N == 128) return small ? launch_solve_n<128, 0>(a, st) : launch_solve_n<128, 1>(a, st);
-    return small ? launch_solve_n<64, 0>(a, st) : launch_solve_n<64, 1>(a, st);
+    // runs of bursts of one kind
+    auto end_of = [&](int b) { return b + 1 < a.bt.nb ? a.bt.b[b + 1].patch0 : a.bt.patches; };
+    auto steps = [&](int b) { return a.ph_steps > 0 && end_of(b) - a.bt.b[b].patch0 <= PHASE_MAX_PATCHES; };
+    hipError_t e = hipSuccess;
+    for (int b = 0; b < a.bt.nb && e == hipSuccess;) {
+        const int base = a.bt.b[b].patch0;
+        const bool ph = steps(b);
+        while (b + 1 < a.bt.nb && steps(b + 1) == ph) ++b;
+        const int n = end_of(b++) - base;
+        if (n == 0) continue;
+        if (ph) e = a.N == 128 ? launch_phase_n<128>(a, base, n, st) : launch_phase_n<64>(a, base, n, st);
+        else if (a.N == 128) e = small ? launch_solve_n<128, 0>(a, base, n, st) : launch_solve_n<128, 1>(a, base, n, st);
+        else e = small ? launch_solve_n<64, 0>(a, base, n, st) : launch_solve_n<64, 1>(a, base, n, st);
+    }
+    return e;
 }
 
 }  // namespace nvsm

@@ -170,6 +170,10 @@ struct SolveArgs {
     int noise_bias = 0;
     double *amp = nullptr;
     double2 *phasor = nullptr;
+    // step schedule of k_phase (plan.hpp, PhaseSteps); 0 steps: k_solve
+    int ph_steps = 0, ph_tpl = 0, ph_early = 0, ph_entries = 0;
+    const unsigned *ph_code = nullptr, *ph_step = nullptr, *ph_crit = nullptr;
+    const int *ph_vslot = nullptr;
     // least-squares refinement (phase_method 1)
     int phase_method = 0, lsq_iters = 0;
     const unsigned *wcode = nullptr;      // sample codes with W indices

@@ -34,8 +34,8 @@ struct DevicePlan {
     int max_sw = 0;
     std::vector<void *> bufs;
     int *W = nullptr, *woff = nullptr, *w_slot = nullptr, *items = nullptr, *units = nullptr,
-        *group_xy = nullptr, *slot = nullptr, *out_idx = nullptr, *lsq_fin = nullptr;
-    unsigned *code = nullptr, *wcode = nullptr;
+        *group_xy = nullptr, *slot = nullptr, *out_idx = nullptr, *lsq_fin = nullptr, *ph_vslot = nullptr;
+    unsigned *code = nullptr, *wcode = nullptr, *ph_code = nullptr, *ph_step = nullptr, *ph_crit = nullptr;
     float2 *twiddle = nullptr;
     float *hann = nullptr, *filt = nullptr;
     ~DevicePlan() {
@@ -323,6 +323,10 @@ nvsm_status get_plan(nvsm_context *ctx, const nvsm_params *p, int slots, DeviceP
         (s = upload(dp.get(), h.w_slot, &dp->w_slot, &msg)) ||
         (s = upload(dp.get(), h.solve_units, &dp->units, &msg)) ||
         (s = upload(dp.get(), h.solve_code, &dp->code, &msg)) ||
+        (s = upload(dp.get(), h.ph.code, &dp->ph_code, &msg)) ||
+        (s = upload(dp.get(), h.ph.step, &dp->ph_step, &msg)) ||
+        (s = upload(dp.get(), h.ph.crit, &dp->ph_crit, &msg)) ||
+        (s = upload(dp.get(), h.ph.vslot, &dp->ph_vslot, &msg)) ||
         (s = upload(dp.get(), h.phase_code, &dp->wcode, &msg)) ||
         (s = upload(dp.get(), h.lsq_fin, &dp->lsq_fin, &msg)) ||
         (s = upload(dp.get(), h.items, &dp->items, &msg)) ||
@@ -452,6 +456,9 @@ hipError_t run_solve(nvsm_context *ctx, DevicePlan *dp, const nvsm_params *p, co
     a.power = power; a.mean_spec = mean_spec; a.bispec = (const float2 *)bispec; a.s_count = dp->h.s_count;
     a.floor = p->stf_floor; a.noise_bias = p->noise_bias == 1; a.amp = amp;
     a.phasor = (double2 *)phasor;
+    a.ph_steps = dp->h.ph.steps; a.ph_tpl = dp->h.ph.tpl; a.ph_early = dp->h.ph.early;
+    a.ph_entries = dp->h.ph.entries;
+    a.ph_code = dp->ph_code; a.ph_step = dp->ph_step; a.ph_crit = dp->ph_crit; a.ph_vslot = dp->ph_vslot;
     a.phase_method = p->phase_method; a.lsq_iters = p->lsq_iters;
     a.wcode = dp->wcode; a.lsq_fin = dp->lsq_fin;
     StageTimer t(ctx, ST_SOLVE, st);

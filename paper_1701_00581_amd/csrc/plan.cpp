@@ -3,8 +3,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <map>
-#include <unordered_map>
 
 namespace nvsm {
 
@@ -169,6 +167,102 @@ bool plan_phase_solve(HostPlan *pl, std::string *err) {
     return true;
 }
 
+void plan_phase_steps(HostPlan *pl) {
+    PhaseSteps &ph = pl->ph;
+    ph = PhaseSteps();
+    const int nW = (int)pl->W.size() / 2, uc = pl->uc, R = pl->R, pw = 2 * uc + 1;
+    // pairs +-v in raster order
+    std::vector<int> pairs;
+    const int side = 2 * R + 1;
+    std::vector<int> pair_of((size_t)side * side, -1);
+    for (int y = 0; y <= R; ++y)
+        for (int x = -R; x <= R; ++x)
+            if (x * x + y * y <= R * R && upper_half(x, y)) {
+                pair_of[(y + R) * side + x + R] = pair_of[(R - y) * side + R - x] = (int)pairs.size() / 2;
+                pairs.push_back(x);
+                pairs.push_back(y);
+            }
+    const int np = (int)pairs.size() / 2;
+    if (np > PH_MAX_PAIRS || pl->max_sw > PH_MAX_SAMPLES || nW >= 1 << 13) return;
+    ph.tpl = std::max(2, (np + 31) / 32);
+    ph.zero = (uc + R + 1) * pw;
+    ph.entries = ph.zero + 1;
+    auto at = [&](int x, int y) { return (y + R) * pw + x + uc; };
+    auto sides = [&](int32_t t, const std::vector<int> &step_of) {    // the later step of a sample's sides
+        return std::max(step_of[(pl->phase_code[t] >> 16) & 0x7fffu], step_of[pl->phase_code[t] & 0x7fffu]);
+    };
+
+    // steps: the groups cut into runs of at most PH_WIDE; step_of by w
+    std::vector<int> step_of(nW, 0), first = {0}, count = {pl->group_wb[1]};
+    for (size_t g = 1; g + 1 < pl->group_wb.size(); ++g)
+        for (int w0 = pl->group_wb[g]; w0 < pl->group_wb[g + 1]; w0 += PH_WIDE) {
+            const int n = std::min(PH_WIDE, pl->group_wb[g + 1] - w0);
+            for (;;) {
+                const int s = (int)first.size();
+                int most = 0;
+                for (int w = w0; w < w0 + n; ++w) {
+                    int fresh = 0;
+                    for (int32_t t = pl->woff[w]; t < pl->woff[w + 1]; ++t) fresh += sides(t, step_of) >= s - 2;
+                    most = std::max(most, fresh);
+                }
+                if (most <= PH_FRESH) break;
+                first.push_back(w0);
+                count.push_back(0);
+            }
+            for (int w = w0; w < w0 + n; ++w) step_of[w] = (int)first.size();
+            first.push_back(w0);
+            count.push_back(n);
+        }
+    ph.steps = (int)first.size();
+    ph.early = step_of[pl->n_inner - 1];
+    ph.vslot.assign(32 * ph.tpl, ph.zero);
+    for (int j = 0; j < np; ++j) ph.vslot[j] = at(pairs[2 * j], pairs[2 * j + 1]);
+    // whole blocks of 64 steps, two to spare for the kernel's look-ahead
+    ph.step.assign(2 * ((ph.steps + 63) / 64 * 64 + 128), 0);
+    for (int s = 1; s < ph.steps; ++s) {
+        const int t0 = pl->woff[first[s]], n = pl->woff[first[s] + count[s]] - t0;
+        ph.step[2 * s] = (uint32_t)first[s] | ((uint32_t)count[s] << 13) | ((uint32_t)n << 17);
+        ph.step[2 * s + 1] = (uint32_t)t0;
+    }
+
+    ph.code.assign((size_t)nW * ph.tpl * 32, PH_NONE | ((uint32_t)ph.zero << 4));
+    ph.crit.assign((size_t)ph.steps * PH_WIDE * 32, 0xffffffffu);
+    for (size_t i = 0; i < ph.crit.size(); i += 4) {
+        ph.crit[i] = (uint32_t)ph.zero | ((uint32_t)ph.zero << 16);
+        ph.crit[i + 1] = PH_NO_SAMPLE;
+    }
+    for (int w = 0; w < 2; ++w) {
+        ph.crit[4 * w] = (uint32_t)at(pl->W[2 * w], pl->W[2 * w + 1]);
+        ph.crit[4 * w + 1] = (uint32_t)at(-pl->W[2 * w], -pl->W[2 * w + 1]);
+    }
+    std::vector<int32_t> v;
+    for (int s = 1; s < ph.steps; ++s)
+        for (int b = 0; b < count[s]; ++b) {
+            const int w = first[s] + b, wx = pl->W[2 * w], wy = pl->W[2 * w + 1];
+            uint32_t *rec = &ph.crit[((size_t)s * PH_WIDE + b) * 32];
+            rec[2] = (uint32_t)at(wx, wy);
+            if (wy <= R) rec[4 + 2] = (uint32_t)at(-wx, -wy);
+            rec[8 + 3] = (uint32_t)w;
+            v.clear();
+            samples_of(wx, wy, R, &v);
+            int fresh = 0;
+            for (size_t k = 0; k < v.size() / 2; ++k) {
+                const int32_t t = pl->woff[w] + (int32_t)k;
+                const int vx = v[2 * k], vy = v[2 * k + 1];
+                const uint32_t slot = (uint32_t)at(wx - vx, wy - vy);
+                if (sides(t, step_of) >= s - 2) {
+                    rec[4 * fresh] = slot | ((uint32_t)at(vx, vy) << 16);
+                    rec[4 * fresh + 1] = (uint32_t)t * 8u;
+                    ++fresh;
+                    continue;
+                }
+                const int j = pair_of[(vy + R) * side + vx + R];
+                ph.code[ph_code_at(w, j % 32, j / 32, ph.tpl)] =
+                    ((uint32_t)(t - pl->woff[first[s]]) << 19) | (upper_half(vx, vy) ? 0u : 1u << 18) | (slot << 4);
+            }
+        }
+}
+
 bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
     if (K < 8 || K > BS_MAX_SLOTS || K % 8) { *err = "slots per wave must be 8..32, a multiple of 8"; return false; }
     pl->slots = K;
@@ -226,6 +320,7 @@ bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
     if (pl->s_count >= (int64_t)1 << 30) { *err = "bispectrum set too large"; return false; }
 
     if (!plan_phase_solve(pl, err)) return false;
+    plan_phase_steps(pl);
 
     // least-squares rounds: the last segment that targets each entry (as
     // its own w or as a side of one of its samples), then the prefixes of
@@ -284,6 +379,8 @@ bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
             groups.push_back(gw);
         }
     }
+    const int vside = 2 * R + 1;
+    auto vat = [&](int vx, int vy) { return (size_t)(vy + R) * vside + vx + R; };
     pl->n_groups = (int)groups.size();
     pl->group_xy.assign((size_t)pl->n_groups * BS_LANES * 2, 0);
     pl->items.clear();
@@ -295,15 +392,17 @@ bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
     for (int gi = 0; gi < pl->n_groups; ++gi) {
         const std::vector<int> &gset = groups[gi];
         int gx0 = 1 << 20, gx1 = -(1 << 20), gy0 = 1 << 20, gy1 = -(1 << 20);
-        std::map<std::pair<int, int>, int> uni;  // (vy, vx) sorted union
+        std::vector<char> uni((size_t)vside * vside, 0);  // union of the v, raster order (vy, vx)
         for (int i : gset) {
             const int wx = pl->W[2 * i], wy = pl->W[2 * i + 1];
             gx0 = std::min(gx0, wx); gx1 = std::max(gx1, wx);
             gy0 = std::min(gy0, wy); gy1 = std::max(gy1, wy);
-            for (size_t j = 0; j < Sw[i].size() / 2; ++j) uni[{Sw[i][2 * j + 1], Sw[i][2 * j]}] = 1;
+            for (size_t j = 0; j < Sw[i].size() / 2; ++j) uni[vat(Sw[i][2 * j], Sw[i][2 * j + 1])] = 1;
         }
         std::vector<std::pair<int, int>> U;  // (vx, vy)
-        for (auto &u : uni) U.push_back({u.first.second, u.first.first});
+        for (int vy = -R; vy <= R; ++vy)
+            for (int vx = -R; vx <= R; ++vx)
+                if (uni[vat(vx, vy)]) U.push_back({vx, vy});
         if (U.empty()) continue;
         // Items: full ones (BS_WAVES chunks of K slots), then one for the
         // rest, whose waves all run ns slots (ns the smallest multiple of 4
@@ -390,7 +489,7 @@ bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
             for (int lane = 0; lane < BS_LANES && !rest.empty(); ++lane)
                 if (lane_w[lane] < 0) { lane_w[lane] = rest.back(); rest.pop_back(); }
         }
-        std::vector<std::unordered_map<int, int>> rank(BS_LANES);
+        std::vector<int32_t> rank((size_t)BS_LANES * vside * vside, -1);   // by lane and v
         for (int lane = 0; lane < BS_LANES; ++lane) {
             int i = lane_w[lane];
             if (i < 0) {
@@ -400,7 +499,7 @@ bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
                 for (int l = 0; l < BS_LANES && i < 0; ++l) i = lane_w[l];
             } else {
                 for (size_t j = 0; j < Sw[i].size() / 2; ++j)
-                    rank[lane][(Sw[i][2 * j + 1] + 64) * 256 + (Sw[i][2 * j] + 64)] = (int)j;
+                    rank[(size_t)lane * vside * vside + vat(Sw[i][2 * j], Sw[i][2 * j + 1])] = (int32_t)j;
             }
             pl->group_xy[((size_t)gi * BS_LANES + lane) * 2 + 0] = pl->W[2 * i];
             pl->group_xy[((size_t)gi * BS_LANES + lane) * 2 + 1] = pl->W[2 * i + 1];
@@ -434,8 +533,8 @@ bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
                     for (int lane = 0; lane < BS_LANES; ++lane) {
                         int32_t o = -1;
                         if (real && lane_w[lane] >= 0) {
-                            auto f = rank[lane].find((vy + 64) * 256 + (vx + 64));
-                            if (f != rank[lane].end()) o = pl->woff[lane_w[lane]] + f->second;
+                            const int32_t f = rank[(size_t)lane * vside * vside + vat(vx, vy)];
+                            if (f >= 0) o = pl->woff[lane_w[lane]] + f;
                         }
                         if (o >= 0) ++covered;
                         pl->out_idx.push_back(o);

@@ -42,6 +42,48 @@ struct Tiling {
 // Rows k start at min(k*s, L-N), k < ceil((L-N)/s)+1 (last tile flush).
 bool make_tiling(int H, int W, int N, int s, Tiling *t);
 
+// Phase recursion in steps of at most PH_WIDE independent w (consecutive in W;
+// step 0 holds the two seeds).  A w's samples whose sides both lie at least
+// three steps back are its bulk, summed ahead of time; the rest, its fresh
+// samples (a side in one of the two steps before; at most PH_FRESH per w, empty
+// steps are put in where there would be more), are added as it is finished.
+//
+// Phasors sit on a raster of the plane's rows -R..u_cut, entry
+// (y + R)(2 u_cut + 1) + x + u_cut, rows below 0 (and y = 0, x < 0) the
+// conjugates of their mirrors; `zero` is one more entry, which holds 0.
+//
+// Bulk: lane l of a half wave holds the pairs +-v number l, l + 32, ... of the
+// half disk 0 < |v| <= R in raster order (vslot: their entries, `zero` past
+// the last).  A w's codes are two runs, words 0..3 and the others (ph_code_at):
+// for pair 32 i + l, the sample's place among those of its step (first w to
+// last, in S order) << 19 | (the sample holds -v) << 18 | the entry of its
+// other side << 4, or PH_NONE | zero << 4 where the pair has no bulk sample.
+// step[2 s] = first w of step s | its count of w << 13 | its count of samples
+// << 17, step[2 s + 1] = the S index of its first sample (step 0 and the
+// padding hold none).
+// crit[(s * PH_WIDE + b) * 8 + k] (uint4) = fresh sample k of w number b of
+// step s: the entry of w - v | that of v << 16, its byte offset in S
+// (PH_NO_SAMPLE: none, entries `zero`); k = 0: the entry of w, k = 1: that of
+// its mirror (else -1); k = 2: w (else -1).  Of step 0 the first words of the
+// first two records are the seeds' entries, the second words those of their
+// mirrors.
+constexpr int PH_FRESH = 8;
+constexpr uint32_t PH_NONE = 1u << 31, PH_NO_SAMPLE = 0x7ffffff8u;
+constexpr int PH_MAX_PAIRS = 224;
+constexpr int PH_BULK = 4;                   // bulk waves of the workgroup, two w each
+constexpr int PH_WIDE = 2 * PH_BULK;
+constexpr int PH_MAX_SAMPLES = 4095 / PH_WIDE;   // of one w, so that a step's places fit 12 bits
+// word of code i of lane l of w's codes
+constexpr int ph_code_at(int w, int l, int i, int tpl) {
+    const int p = tpl < 4 ? tpl : 4;
+    return w * tpl * 32 + (i < p ? l * p + i : 32 * p + l * (tpl - p) + i - p);
+}
+struct PhaseSteps {
+    int steps = 0, tpl = 0, entries = 0, zero = 0, early = 0;
+    std::vector<uint32_t> code, step, crit;
+    std::vector<int32_t> vslot;
+};
+
 struct HostPlan {
     int N = 0, uc = 0, R = 0;
     // W in storage order as (wx, wy) pairs, and the S offset of each w.
@@ -116,6 +158,10 @@ struct HostPlan {
     std::vector<float> hann;            // N: periodic Hann taper
     std::vector<float> filt;            // |W|: diffraction OTF at |w|/(N/2)
     double hann_sum2 = 0;               // sum of the 2-D taper
+
+    // Step schedule of the phase recursion (k_phase), for v radii of at most
+    // PH_MAX_PAIRS pairs +-v (R <= 12); ph.steps == 0 otherwise.
+    PhaseSteps ph;
 };
 
 // Builds everything above; returns false with *err set on bad sizes.
@@ -126,6 +172,9 @@ bool build_plan(int N, int uc, int R, int slots, HostPlan *out, std::string *err
 // codes, the padded code blocks and the units.  build_plan calls it after
 // forming the groups; returns false with *err set on bad sizes.
 bool plan_phase_solve(HostPlan *pl, std::string *err);
+
+// The step schedule (ph) for the groups in group_wb, N, uc and R.
+void plan_phase_steps(HostPlan *pl);
 
 // S in storage order, 4 ints per entry (wx, wy, vx, vy).
 void enumerate_S(int uc, int R, std::vector<int32_t> *wv);

@@ -1,0 +1,85 @@
+"""The phase recursion in steps (k_phase) against the FP64 oracle, at the edges
+of its range: 1 to 4 pairs +-v per lane, exactly full lanes and remainders, the
+smallest W, and a mean bispectrum that is zero for some w."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_helpers import phase_rms, say
+
+pytestmark = pytest.mark.gpu
+
+# Both sides work in FP64 from the same float32 inputs.  A phasor is the unit of
+# a sum of coherent samples, so its error is a few 2^-53 beyond that of the
+# phasors it reads; along a chain of about 1000 steps that adds up to less
+# than 1000 x 20 x 2^-53 = 2e-12 rad.
+TOL = 2e-12
+
+
+@pytest.mark.parametrize("N,u_cut,R", [(128, 63, 12), (128, 63, 9), (128, 63, 1), (128, 20, 12), (128, 3, 2),
+                                       (64, 31, 12), (64, 31, 11), (64, 31, 8), (64, 2, 1)])
+def test_phase_steps_against_the_oracle(N, u_cut, R):
+    import torch
+    import paper_1701_00581_amd as nv
+    p = nv.default_params(N, u_cut=u_cut, v_radius=R)
+    Wset, S, woff = oracle.bispectrum_set(u_cut, R)
+    rng = np.random.default_rng(17 + N + u_cut + R)
+    P = 3
+    B = np.zeros((P, len(S)), np.complex128)
+    M = np.zeros((P, 2), np.complex128)
+    ix = lambda a, b: (b % N) * N + a % N  # noqa: E731
+    for k in range(P):
+        phi = rng.uniform(-np.pi, np.pi, N * N)
+        phi[ix(-Wset[:, 0], -Wset[:, 1])] = -phi[ix(Wset[:, 0], Wset[:, 1])]
+        wx, wy, vx, vy = S.T
+        arg = phi[ix(wx - vx, wy - vy)] + phi[ix(vx, vy)] - phi[ix(wx, wy)]
+        B[k] = (1 + 9 * rng.random(len(S))) * np.exp(1j * (arg + 0.3 * rng.standard_normal(len(S))))
+        M[k] = 2 * np.exp(1j * phi[[1, N]])
+    B[1, woff[len(Wset) - 2]:woff[len(Wset) - 1]] = 0      # a w whose sum is 0 gets the phasor 1
+    M[2, 1] = 0
+    B = B.astype(np.complex64)
+    s = nv.Session(p, N, N + (P - 1) * p.stride, 1)
+    assert s.info.patches == P and s.info.s_count == len(S)
+    s.bispec.copy_(torch.from_numpy(np.ascontiguousarray(B).view(np.float32).reshape(P, len(S), 2)))
+    s.mean_spec.copy_(torch.from_numpy(M.astype(np.complex64).view(np.float32).reshape(P, 2, 2)))
+    s.power.fill_(1.0)
+    stf = torch.ones(N, N, dtype=torch.float64, device="cuda")
+    for _ in range(2):                                     # a second launch finds LDS in use
+        s.phasor.fill_(float("nan"))
+        s.solve(stf)
+    e = s.phasor.cpu().numpy()
+    e = e[..., 0] + 1j * e[..., 1]
+    for k in range(P):
+        M32 = M[k].astype(np.complex64)
+        ref = oracle.phase_recursion(B[k].astype(np.complex128), M32[0], M32[1], Wset, S, woff, N)
+        rms, worst = phase_rms(e[k], ref)
+        say(f"N {N} u_cut {u_cut} R {R} patch {k}: rms {rms:.1e} worst {worst:.1e}")
+        assert rms <= TOL and np.max(np.abs(np.abs(e[k]) - 1)) < 1e-12
+    assert torch.equal(s.amp, torch.ones_like(s.amp))
+    s.close()
+
+
+def test_batch_of_both_kinds_equals_alone():
+    """A batch whose bursts lie on both sides of the patch count (256) that
+    separates the two phase kernels: each burst's phasors are those of the
+    same burst alone, bit for bit."""
+    import torch
+    import paper_1701_00581_amd as nv
+    p = nv.default_params(64, v_radius=4, stride=32)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    shapes = [(4, 96, 128), (3, 32 * 17, 32 * 19), (2, 32 * 17, 32 * 17), (3, 64, 64), (2, 32 * 18, 32 * 17)]
+    assert [nv.nvsm_plan(p, h, w, f).patches for f, h, w in shapes] == [6, 16 * 18, 256, 1, 17 * 16]
+    bursts = []
+    for f, h, w in shapes:
+        fr = 1000 * (1 + 0.2 * torch.rand(f, h, w, device="cuda", generator=g))
+        bursts.append((fr, torch.ones(64, 64, dtype=torch.float64, device="cuda"), torch.zeros(h, w, device="cuda")))
+    ctx = nv.nvsm_create(0)
+    ws = torch.empty(nv.nvsm_batch_plan(p, shapes)[1], dtype=torch.uint8, device="cuda")
+    nv.nvsm_reconstruct_batch(ctx, p, bursts, ws)
+    together = [b[2].clone() for b in bursts]
+    for (fr, st, out), ref in zip(bursts, together):
+        out.zero_()
+        nv.nvsm_reconstruct(ctx, p, fr, st, out, ws)
+        assert torch.equal(out, ref)
+    torch.cuda.synchronize()
+    nv.nvsm_destroy(ctx)
