@@ -69,6 +69,20 @@ __device__ __forceinline__ double wave_total_lane63(double v) {
     return v;
 }
 
+// Sums of x and of y over the 64 lanes: lane 31 gets the total of x, lane 63
+// that of y (the halves exchanged first, so that both sums run as one).
+__device__ __forceinline__ double wave_total_pair(double x, double y) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+    double v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    v += dpp_d<0xb1>(v);     // quad_perm [1,0,3,2]
+    v += dpp_d<0x4e>(v);     // quad_perm [2,3,0,1]
+    v += dpp_d<0x141>(v);    // row_half_mirror
+    v += dpp_d<0x140>(v);    // row_mirror: every lane holds its row sum
+    v += dpp_d<0x142>(v);    // row_bcast:15: row 1 gets rows 0 + 1, row 3 rows 2 + 3
+    return v;
+}
+
 // Sums of x and of y over each half wave: the rows of 16 lanes get, in turn,
 // the first half's x and y and the second half's x and y (x's and y's rows
 // exchanged first, so that both sums run as one).
@@ -778,6 +792,203 @@ hipError_t launch_solve_t(const SolveArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
+// The same steps with one w per wave and the pairs +-v over its lanes (at
+// most LSQ_MAX_PAIRS pairs, R <= 12; k_lsq takes the others): a w has at most
+// one sample of each pair, so lane l always meets the same TPL pairs.  Their
+// phasors e(v) stay in registers for the step, and so do the sums of the
+// sides v (one of the two LDS adds and one of the two gathers of a sample
+// gone); only the sides w - v are added in LDS, where a wave's lanes never
+// share a target.  Those adds are 64-bit fixed point like k_lsq's (units of
+// at most sum |Re B| + |Im B| over 2^61, k_lsq's 2^60), but formed by one FP64
+// addition: x + 1.5 2^52 holds the integer nearest x in its low bits for
+// |x| < 2^51, which all but the few samples above 1/2000 of that sum meet;
+// those are converted in full.  The sums over v and over a w's own samples
+// stay in FP64 until a wave's total is added.  New phasors wait in the output
+// array until the step ends (in registers they made the kernel spill).
+// k_lsq issues about 110 instructions a sample, this about 55.
+// 10 steps of 81 patches (N = 128, R = 10): 14.8 -> 7.4 ms (9.5 with 8 waves); the
+// phasors are 7e-14 from the FP64 ones (k_lsq 2.6e-13).  VALU issue is at 0.66
+// and the LDS pipe at 0.56 of the cycles, three quarters of that conflicts of
+// the gathers and adds, whose entries lie in order of |w|.
+constexpr int LQ_NT = 1024, LQ_NWAVE = LQ_NT / 64, LQ_SLOTS = (LSQ_MAXW + LQ_NT - 1) / LQ_NT;
+template <int TPL>
+__global__ __launch_bounds__(LQ_NT) void k_lsq_pairs(int nW, int n_inner, int iters, const int *__restrict__ woff,
+                                                  const unsigned *__restrict__ code, const int *__restrict__ vidx,
+                                                  const int *__restrict__ fin, const float2 *__restrict__ bispec,
+                                                  int64_t s_count, double2 *__restrict__ phasor) {
+    __shared__ double2 e[LSQ_MAXW];
+    __shared__ unsigned long long acc[2 * LSQ_ACC];
+    const int patch = blockIdx.x;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    double2 *ph = phasor + (size_t)patch * nW;
+    const float2 *B = bispec + (size_t)patch * s_count;
+    for (int i = tid; i < nW; i += LQ_NT) e[i] = ph[i];
+    // sum |Re B| + |Im B| (fixed summation order; eight loads in flight per
+    // thread: clamped past the end, and weighted 0)
+    double s1 = 0.0;
+    for (int64_t t0 = tid; t0 < s_count; t0 += 8 * LQ_NT) {
+        float2 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = B[min(t0 + (int64_t)k * LQ_NT, s_count - 1)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (t0 + (int64_t)k * LQ_NT < s_count) s1 += fabs((double)v[k].x) + fabs((double)v[k].y);
+    }
+    s1 = wave_sum_d(s1);
+    double *red = (double *)acc;                 // (before the accumulators are used)
+    if (lane == 0) red[wave] = s1;
+    __syncthreads();
+    s1 = 0.0;
+#pragma unroll
+    for (int k = 0; k < LQ_NWAVE; ++k) s1 += red[k];
+    if (!(s1 > 0.0) || !isfinite(s1)) return;          // no usable samples: the phasors stay
+    const double scale = scalbn(1.0, 61 - ilogb(s1));  // s1 scale in [2^61, 2^62)
+    const int ring = LSQ_ACC - n_inner;                 // >= the plan's live span (checked on the host)
+    // accumulator of entry x: the inner disk first, then the ring
+    auto slot = [&](unsigned x) __attribute__((always_inline)) {
+        if ((int)x < n_inner) return x;
+        int q = (int)x - n_inner;
+        if (q >= ring) q -= ring;                       // x - n_inner < |W| < 2 ring
+        return (unsigned)(n_inner + q);
+    };
+    // a total already in units of 1 / scale
+    auto add = [&](unsigned k, double x, double y) __attribute__((always_inline)) {
+        atomicAdd(&acc[2 * k], (unsigned long long)__double2ll_rn(x));
+        atomicAdd(&acc[2 * k + 1], (unsigned long long)__double2ll_rn(y));
+    };
+    // |x| < 2^51 as a 64-bit integer (nearest)
+    auto fixed = [&](double x) __attribute__((always_inline)) {
+        const double m = x + 0x1.8p52;
+        return ((unsigned long long)((unsigned)__double2hiint(m) - 0x43380000u) << 32) | (unsigned)__double2loint(m);
+    };
+    auto flip = [](double y, unsigned bit31) __attribute__((always_inline)) {
+        return __longlong_as_double(__double_as_longlong(y) ^ ((long long)(bit31 & 0x80000000u) << 32));
+    };
+    int vi[TPL];
+#pragma unroll
+    for (int i = 0; i < TPL; ++i) vi[i] = vidx[64 * i + lane];
+    const unsigned *cl = code + lane * TPL;
+    const int rounds = (nW + LSQ_ROUND - 1) / LSQ_ROUND;
+    for (int it = 0; it < iters; ++it) {
+        __syncthreads();                               // `red` was read, or the table rewritten
+        for (int i = tid; i < 2 * LSQ_ACC; i += LQ_NT) acc[i] = 0ull;
+        double2 ev[TPL], av[TPL];                      // e(v), and the sums of the sides v (scaled)
+#pragma unroll
+        for (int i = 0; i < TPL; ++i) {
+            ev[i] = e[max(vi[i], 0)];
+            av[i] = make_double2(0.0, 0.0);
+        }
+        __syncthreads();
+        unsigned cd[2][TPL];
+        float2 bb[2][TPL];
+        // codes of w, then (a w later) the samples they place; a lane without
+        // one reads past w's samples, i.e. 0.  Past the last w: no samples.
+        auto load_c = [&](int w, int k) __attribute__((always_inline)) {
+            const unsigned *q = cl + (size_t)min(w, nW - 1) * (64 * TPL);
+#pragma unroll
+            for (int i = 0; i < TPL; ++i) cd[k][i] = q[i];
+        };
+        auto load_b = [&](int w, int k) __attribute__((always_inline)) {
+            const int o = woff[min(w, nW)], n = woff[min(w + 1, nW)] - o;
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(B + o), (short)0, n * (int)sizeof(float2), 0x00020000);
+#pragma unroll
+            for (int i = 0; i < TPL; ++i) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)((cd[k][i] >> 20) & 0xff8u), 0, 0);
+                bb[k][i] = make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+            }
+        };
+        // this wave's w: wave, wave + LQ_NWAVE, ... (LSQ_ROUND / LQ_NWAVE to a round)
+        load_c(wave, 0);
+        load_b(wave, 0);
+        load_c(wave + LQ_NWAVE, 1);
+        for (int r = 0; r < rounds; ++r) {
+            constexpr int PER = LSQ_ROUND / LQ_NWAVE;
+            static_assert(PER % 2 == 0, "the register sets alternate");
+#pragma unroll
+            for (int m = 0; m < PER; ++m) {
+                const int w = r * LSQ_ROUND + m * LQ_NWAVE + wave, k = m % 2;
+                load_b(w + LQ_NWAVE, k ^ 1);
+                if (w < nW) {
+                    double2 cw = e[w];
+                    double2 a[TPL];
+#pragma unroll
+                    for (int i = 0; i < TPL; ++i) a[i] = *(const double2 *)((const char *)e + (cd[k][i] & 0x1fff0u));
+                    cw.x *= scale;
+                    cw.y *= scale;
+                    double gx = 0.0, gy = 0.0;
+#pragma unroll
+                    for (int i = 0; i < TPL; ++i) {
+                        const unsigned c = cd[k][i];
+                        const double bx = (double)bb[k][i].x, by = (double)bb[k][i].y;
+                        const double ax = a[i].x, ay = flip(a[i].y, c << 10);        // e(w - v)
+                        const double vx = ev[i].x, vy = flip(ev[i].y, c << 9);       // e(+-v)
+                        // own: e(w - v) e(v) conj(B)
+                        const double px = fma(ax, vx, -ay * vy), py = fma(ax, vy, ay * vx);
+                        gx = fma(px, bx, fma(py, by, gx));
+                        gy = fma(py, bx, fma(-px, by, gy));
+                        // e(w) B
+                        const double qx = fma(cw.x, bx, -cw.y * by), qy = fma(cw.x, by, cw.y * bx);
+                        // side v: conj(e(w - v)) e(w) B, conjugated for -v
+                        av[i].x = fma(ax, qx, fma(ay, qy, av[i].x));
+                        av[i].y += flip(fma(ax, qy, -ay * qx), c << 9);
+                        // side w - v: conj(e(v)) e(w) B, conjugated for a mirror
+                        if (c < (LSQ_NONE << 23)) {
+                            const unsigned k2 = slot((c >> 4) & 0x1fffu);
+                            const double rx = fma(vx, qx, vy * qy), ry = flip(fma(vx, qy, -vy * qx), c << 10);
+                            if (fabs(qx) < 0x1p50 && fabs(qy) < 0x1p50) {
+                                atomicAdd(&acc[2 * k2], fixed(rx));
+                                atomicAdd(&acc[2 * k2 + 1], fixed(ry));
+                            } else {
+                                add(k2, rx, ry);
+                            }
+                        }
+                    }
+                    const double g = wave_total_pair(gx, gy);
+                    if ((lane & 31) == 31)
+                        atomicAdd(&acc[2 * slot((unsigned)w) + (lane >> 5)], (unsigned long long)__double2ll_rn(g * scale));
+                }
+                load_c(w + 2 * LQ_NWAVE, k);
+            }
+            const bool last = r + 1 == rounds;
+            if (last) {
+#pragma unroll
+                for (int i = 0; i < TPL; ++i)
+                    if (vi[i] >= 0) add((unsigned)vi[i], av[i].x, av[i].y);
+            }
+            __syncthreads();
+            // entries no later round targets: new phasors, accumulators cleared
+            // for the ring entries that will take their slots
+            const int f0 = fin[r], f1 = fin[r + 1];
+#pragma unroll
+            for (int j = 0; j < LQ_SLOTS; ++j) {
+                const int u = tid + LQ_NT * j;
+                if (u >= 2 && u < nW && ((u >= f0 && u < f1) || (last && u < n_inner))) {
+                    const unsigned k = slot((unsigned)u);
+                    const double gx = (double)(long long)acc[2 * k];
+                    const double gy = (double)(long long)acc[2 * k + 1];
+                    acc[2 * k] = 0ull;
+                    acc[2 * k + 1] = 0ull;
+                    const double2 old = e[u];
+                    double2 nw = old;
+                    const double m = sqrt(gx * gx + gy * gy);
+                    if (m > 0.0) {
+                        const double sx = gx / m + old.x, sy = gy / m + old.y;
+                        const double rr = sqrt(sx * sx + sy * sy);
+                        if (rr > 0.0) nw = make_double2(sx / rr, sy / rr);
+                    }
+                    ph[u] = nw;
+                }
+            }
+            __syncthreads();                               // cleared before the next round adds
+        }
+        // (every thread reads back what it wrote itself)
+        for (int u = tid; u < nW; u += LQ_NT) e[u] = ph[u];
+    }
+}
+
 template <int N, int TPL>
 hipError_t launch_phase_t(const SolveArgs &a, int base, int patches, hipStream_t st) {
     const PhaseArgs pa = {a.ph_steps, a.ph_early, a.ph_entries, (int)a.s_count,
@@ -833,6 +1044,14 @@ constexpr int PHASE_MAX_PATCHES = 256;
 hipError_t launch_lsq(const SolveArgs &a, hipStream_t st) {
     if (a.nW > LSQ_MAXW || a.nW < 2 || a.lsq_iters < 1 || !a.lsq_fin) return hipErrorInvalidValue;
     if (a.n_inner < 2 || a.n_inner > LSQ_ACC / 2 || 2 * (LSQ_ACC - a.n_inner) <= a.nW) return hipErrorInvalidValue;
+    auto pairs = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(a.bt.patches), dim3(LQ_NT), 0, st, a.nW, a.n_inner, a.lsq_iters, a.woff,
+                           a.lq_code, a.lq_vidx, a.lsq_fin, a.bispec, a.s_count, a.phasor);
+        return hipGetLastError();
+    };
+    if (a.lq_tpl == 2) return pairs(k_lsq_pairs<2>);
+    if (a.lq_tpl == 3) return pairs(k_lsq_pairs<3>);
+    if (a.lq_tpl == 4) return pairs(k_lsq_pairs<4>);
     hipLaunchKernelGGL(k_lsq, dim3(a.bt.patches), dim3(LSQ_NT), 0, st, a.nW, a.n_inner, a.lsq_iters, a.woff, a.wcode,
                        a.lsq_fin, a.bispec, a.s_count, a.phasor);
     return hipGetLastError();

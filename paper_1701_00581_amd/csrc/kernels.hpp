@@ -177,6 +177,9 @@ struct SolveArgs {
     // least-squares refinement (phase_method 1)
     int phase_method = 0, lsq_iters = 0;
     const unsigned *wcode = nullptr;      // sample codes with W indices
+    int lq_tpl = 0;                       // pairs' samples (plan.hpp, LsqPairs); 0: k_lsq
+    const unsigned *lq_code = nullptr;
+    const int *lq_vidx = nullptr;
     const int *lsq_fin = nullptr;         // flushed prefix before each round (see plan.hpp)
     SolveArgs() = default;
     SolveArgs(const SolveArgs &o, int method) : SolveArgs(o) { phase_method = method; }

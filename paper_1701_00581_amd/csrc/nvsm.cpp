@@ -34,8 +34,9 @@ struct DevicePlan {
     int max_sw = 0;
     std::vector<void *> bufs;
     int *W = nullptr, *woff = nullptr, *w_slot = nullptr, *items = nullptr, *units = nullptr,
-        *group_xy = nullptr, *slot = nullptr, *out_idx = nullptr, *lsq_fin = nullptr, *ph_vslot = nullptr;
-    unsigned *code = nullptr, *wcode = nullptr, *ph_code = nullptr, *ph_step = nullptr, *ph_crit = nullptr;
+        *group_xy = nullptr, *slot = nullptr, *out_idx = nullptr, *lsq_fin = nullptr, *ph_vslot = nullptr,
+        *lq_vidx = nullptr;
+    unsigned *code = nullptr, *wcode = nullptr, *ph_code = nullptr, *ph_step = nullptr, *ph_crit = nullptr, *lq_code = nullptr;
     float2 *twiddle = nullptr;
     float *hann = nullptr, *filt = nullptr;
     ~DevicePlan() {
@@ -328,6 +329,8 @@ nvsm_status get_plan(nvsm_context *ctx, const nvsm_params *p, int slots, DeviceP
         (s = upload(dp.get(), h.ph.crit, &dp->ph_crit, &msg)) ||
         (s = upload(dp.get(), h.ph.vslot, &dp->ph_vslot, &msg)) ||
         (s = upload(dp.get(), h.phase_code, &dp->wcode, &msg)) ||
+        (s = upload(dp.get(), h.lsq.code, &dp->lq_code, &msg)) ||
+        (s = upload(dp.get(), h.lsq.vidx, &dp->lq_vidx, &msg)) ||
         (s = upload(dp.get(), h.lsq_fin, &dp->lsq_fin, &msg)) ||
         (s = upload(dp.get(), h.items, &dp->items, &msg)) ||
         (s = upload(dp.get(), h.group_xy, &dp->group_xy, &msg)) ||
@@ -461,6 +464,7 @@ hipError_t run_solve(nvsm_context *ctx, DevicePlan *dp, const nvsm_params *p, co
     a.ph_code = dp->ph_code; a.ph_step = dp->ph_step; a.ph_crit = dp->ph_crit; a.ph_vslot = dp->ph_vslot;
     a.phase_method = p->phase_method; a.lsq_iters = p->lsq_iters;
     a.wcode = dp->wcode; a.lsq_fin = dp->lsq_fin;
+    a.lq_tpl = dp->h.lsq.tpl; a.lq_code = dp->lq_code; a.lq_vidx = dp->lq_vidx;
     StageTimer t(ctx, ST_SOLVE, st);
     return launch_solve(a, st);
 }

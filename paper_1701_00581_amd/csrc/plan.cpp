@@ -167,6 +167,36 @@ bool plan_phase_solve(HostPlan *pl, std::string *err) {
     return true;
 }
 
+void plan_lsq_pairs(HostPlan *pl) {
+    LsqPairs &lq = pl->lsq;
+    lq = LsqPairs();
+    const int nW = (int)pl->W.size() / 2, R = pl->R, side = 2 * R + 1;
+    // pairs in raster order of their upper-half member
+    std::vector<int> pair_of((size_t)side * side, -1);
+    int np = 0;
+    for (int y = 0; y <= R; ++y)
+        for (int x = -R; x <= R; ++x)
+            if (x * x + y * y <= R * R && upper_half(x, y))
+                pair_of[(y + R) * side + x + R] = pair_of[(R - y) * side + R - x] = np++;
+    if (np > LSQ_MAX_PAIRS || pl->max_sw >= (int)LSQ_NONE || nW >= 1 << 13) return;
+    lq.tpl = std::max(2, (np + 63) / 64);
+    lq.vidx.assign(64 * lq.tpl, -1);
+    for (int i = 0; i < pl->n_inner; ++i)
+        lq.vidx[pair_of[(pl->W[2 * i + 1] + R) * side + pl->W[2 * i] + R]] = i;
+    lq.code.assign((size_t)nW * 64 * lq.tpl, LSQ_NONE << 23);
+    std::vector<int32_t> v;
+    for (int w = 0; w < nW; ++w) {
+        v.clear();
+        samples_of(pl->W[2 * w], pl->W[2 * w + 1], R, &v);
+        for (size_t k = 0; k < v.size() / 2; ++k) {
+            const uint32_t c = pl->phase_code[pl->woff[w] + k];
+            const int j = pair_of[(v[2 * k + 1] + R) * side + v[2 * k] + R];
+            lq.code[((size_t)w * 64 + j % 64) * lq.tpl + j / 64] =
+                ((uint32_t)k << 23) | (((c >> 15) & 1u) << 22) | ((c >> 31) << 21) | (((c >> 16) & 0x7fffu) << 4);
+        }
+    }
+}
+
 void plan_phase_steps(HostPlan *pl) {
     PhaseSteps &ph = pl->ph;
     ph = PhaseSteps();
@@ -321,6 +351,7 @@ bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
 
     if (!plan_phase_solve(pl, err)) return false;
     plan_phase_steps(pl);
+    plan_lsq_pairs(pl);
 
     // least-squares rounds: the last segment that targets each entry (as
     // its own w or as a side of one of its samples), then the prefixes of

@@ -84,6 +84,20 @@ struct PhaseSteps {
     std::vector<int32_t> vslot;
 };
 
+// Least-squares steps with one w per wave and the pairs +-v over its lanes
+// (k_lsq_pairs), for at most LSQ_MAX_PAIRS pairs (R <= 12); tpl 0 otherwise.
+// Pair number 64 i + l (as PhaseSteps) belongs to lane l: vidx[64 i + l] is v's
+// index in W (-1 past the last pair), and code[(w * 64 + l) * tpl + i] its
+// sample of S(w): place in S(w) << 23 | (the sample holds -v) << 22 | (w - v
+// has its mirror in W) << 21 | that index in W << 4; place LSQ_NONE: none.
+constexpr int LSQ_MAX_PAIRS = 256;
+constexpr uint32_t LSQ_NONE = 511;
+struct LsqPairs {
+    int tpl = 0;
+    std::vector<uint32_t> code;
+    std::vector<int32_t> vidx;
+};
+
 struct HostPlan {
     int N = 0, uc = 0, R = 0;
     // W in storage order as (wx, wy) pairs, and the S offset of each w.
@@ -162,6 +176,7 @@ struct HostPlan {
     // Step schedule of the phase recursion (k_phase), for v radii of at most
     // PH_MAX_PAIRS pairs +-v (R <= 12); ph.steps == 0 otherwise.
     PhaseSteps ph;
+    LsqPairs lsq;
 };
 
 // Builds everything above; returns false with *err set on bad sizes.
@@ -172,6 +187,9 @@ bool build_plan(int N, int uc, int R, int slots, HostPlan *out, std::string *err
 // codes, the padded code blocks and the units.  build_plan calls it after
 // forming the groups; returns false with *err set on bad sizes.
 bool plan_phase_solve(HostPlan *pl, std::string *err);
+
+// The pairs' samples (lsq) for W, woff, phase_code and R.
+void plan_lsq_pairs(HostPlan *pl);
 
 // The step schedule (ph) for the groups in group_wb, N, uc and R.
 void plan_phase_steps(HostPlan *pl);

@@ -83,3 +83,46 @@ def test_batch_of_both_kinds_equals_alone():
         assert torch.equal(out, ref)
     torch.cuda.synchronize()
     nv.nvsm_destroy(ctx)
+
+
+@pytest.mark.parametrize("N,u_cut,R,spike", [(128, 63, 12, 1), (128, 40, 9, 1), (64, 31, 8, 1e7), (64, 20, 12, 1e3),
+                                             (64, 5, 4, 1), (64, 2, 1, 1)])
+def test_least_squares_pairs_against_the_oracle(N, u_cut, R, spike):
+    """The least-squares steps with pairs over the lanes (k_lsq_pairs): 1 to 4
+    pairs per lane, W shorter than a round, and a sample that outweighs the
+    others (its adds take the full conversion)."""
+    import torch
+    import paper_1701_00581_amd as nv
+    p = nv.default_params(N, u_cut=u_cut, v_radius=R, phase_method=1, lsq_iters=3)
+    Wset, S, woff = oracle.bispectrum_set(u_cut, R)
+    rng = np.random.default_rng(N + u_cut + R)
+    phi = rng.uniform(-np.pi, np.pi, N * N)
+    ix = lambda a, b: (b % N) * N + a % N  # noqa: E731
+    phi[ix(-Wset[:, 0], -Wset[:, 1])] = -phi[ix(Wset[:, 0], Wset[:, 1])]
+    wx, wy, vx, vy = S.T
+    arg = phi[ix(wx - vx, wy - vy)] + phi[ix(vx, vy)] - phi[ix(wx, wy)]
+    B = (1 + 9 * rng.random(len(S))) * np.exp(1j * (arg + 0.5 * rng.standard_normal(len(S))))
+    B[len(S) // 2] *= spike
+    B = B.astype(np.complex64)
+    M = (2 * np.exp(1j * phi[[1, N]])).astype(np.complex64)
+    s = nv.Session(p, N, N, 1)
+    s.bispec.copy_(torch.from_numpy(B.view(np.float32).reshape(1, len(S), 2)))
+    s.mean_spec.copy_(torch.from_numpy(M.view(np.float32).reshape(1, 2, 2)))
+    s.power.fill_(1.0)
+    s.solve(torch.ones(N, N, dtype=torch.float64, device="cuda"))
+    e = s.phasor.cpu().numpy()[0]
+    e = e[..., 0] + 1j * e[..., 1]
+    first = s.phasor.clone()
+    s.solve(torch.ones(N, N, dtype=torch.float64, device="cuda"))
+    assert torch.equal(first, s.phasor)                    # integer adds: repeatable
+    s.close()
+    B64 = B.astype(np.complex128)
+    ref = oracle.phase_recursion(B64, M[0], M[1], Wset, S, woff, N)
+    ref = oracle.phase_least_squares(B64, ref, Wset, S, woff, 3)
+    rms, worst = phase_rms(e, ref)
+    say(f"lsq N {N} u_cut {u_cut} R {R}: rms {rms:.1e} worst {worst:.1e}")
+    # an add is off by half a unit, s1 2^-62 (s1 = sum |Re B| + |Im B|); a sum
+    # has at most a few hundred adds and |g| at least 1 here, and a step at
+    # most doubles what the one before left
+    s1 = float(np.abs(B64.real).sum() + np.abs(B64.imag).sum())
+    assert worst <= 8 * (300 * s1 * 2.0 ** -62 + TOL)
