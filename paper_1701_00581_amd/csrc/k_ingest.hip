@@ -56,6 +56,9 @@ template <typename T> struct Quad<T, false> {
     __device__ float operator[](int i) const { return e[i]; }
 };
 
+// s + |I|^2
+__device__ __forceinline__ float add_power(float s, float2 I) { return fmaf(I.x, I.x, fmaf(I.y, I.y, s)); }
+
 // Storage position of frequency k after the transform (as fft_pos), in
 // unsigned arithmetic for indices the optimizer cannot bound.
 template <int N>
@@ -70,7 +73,23 @@ __device__ __forceinline__ unsigned fft_pos_u(unsigned k) {
 // flight at its entry).
 template <typename T> constexpr int ingest_threads() { return 512; }
 
-template <int N, typename T, bool VEC>
+// A launch of few workgroups (FINE_MAX_WGS) leaves most CUs idle while each
+// transforms its 10 frame pairs in turn.  Then (FINE) a workgroup takes one
+// pair and leaves the sums over frames to the passes that combine the frame
+// groups: it keeps, per frame, what those need beyond the record, the values
+// of row N/2 (ux = 0..N/2; the others are their conjugates) and the mean
+// level, in the memory of the partials it does not write:
+// fine[record][N + 4] floats.  Those passes then add each group's frames in
+// the same order by the same operations, so every sum is the same bit for bit.
+// 12 patches of 101 frames at N = 128: 142 + 5 -> 60 + 18 us (transforms, sums);
+// one 64 x 64 patch of 100 frames 41 + 5 -> 8 + 9 us.  The line lies where
+// reading the records again begins to cost more than the idle CUs did: at
+// N = 128 125 workgroups 160 -> 148 us, 180 170 -> 225; at N = 64 125 50 -> 36,
+// 180 53 -> 52.
+constexpr int FINE_MAX_WGS = 128, FINE_MAX_FRAMES = 20;   // (frames of a group)
+template <int N> constexpr int fine_stride() { return N + 4; }
+
+template <int N, typename T, bool VEC, bool FINE>
 __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable bt, int stride, int chunk_frames, int window,
                                                float inv_wsum, const float2 *__restrict__ twiddle,
                                                const float *__restrict__ hann,
@@ -168,9 +187,16 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
         for (int k = 0; k < IT / 64; ++k) { mua += red[0][k]; mub += red[1][k]; }
         mua *= inv_wsum;
         mub *= inv_wsum;
+        float2 *const fine_a = (float2 *)(ppart + (size_t)(bd.spec0 + (int64_t)lpatch * F + fa) * fine_stride<N>());
+        float2 *const fine_b = fine_a + fine_stride<N>() / 2;
         if (tid == 0) {
-            kahan_add(mus, muc, mua);
-            if (hasb) kahan_add(mus, muc, mub);
+            if constexpr (FINE) {
+                fine_a[HALF + 1].x = mua;
+                if (hasb) fine_b[HALF + 1].x = mub;
+            } else {
+                kahan_add(mus, muc, mua);
+                if (hasb) kahan_add(mus, muc, mub);
+            }
         }
         // the mean-removed, tapered pixels to LDS (the previous pair's
         // transform was read before the loop's last barrier)
@@ -193,7 +219,7 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
         // last frame is loaded again, unused; a missing second frame's stores
         // go to the first frame's record, ahead of the first frame's own), so
         // the compiler knows how many are in flight.
-        load_pair(min(fa + 2, f1 - 1));
+        if constexpr (!FINE) load_pair(min(fa + 2, f1 - 1));
         fft2d_lds_inline<N, IT>(z, tw);
         // records of the two frames: wave-uniform bases, 32-bit lane offsets
         const gptr_m rec_a = uniform_ptr_m(spectra + spec_patch + (size_t)fa * FS);
@@ -216,18 +242,23 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
                 const unsigned uy = j / N, ux = j % N;
                 float2 Ia, Ib;
                 split(ux, uy, Ia, Ib);
-                ps[k] += Ia.x * Ia.x + Ia.y * Ia.y;
-                if (hasb) ps[k] += Ib.x * Ib.x + Ib.y * Ib.y;
+                if constexpr (!FINE) {
+                    ps[k] = add_power(ps[k], Ia);
+                    if (hasb) ps[k] = add_power(ps[k], Ib);
+                } else if (k * IT >= HALF * N && ux <= HALF) {
+                    fine_a[ux] = Ia;
+                    if (hasb) fine_b[ux] = Ib;
+                }
                 if (k * IT < HALF * N) {
                     const unsigned o = ((uy + SPEC_NEG_ROWS) * N + ux) * (unsigned)sizeof(float2);
                     store_global_f2(rec_b, o, Ib);
                     store_global_f2(rec_a, o, Ia);
                 }
-                if (k * IT + tid == 1) {   // u = (1, 0)
+                if (!FINE && k * IT + tid == 1) {   // u = (1, 0)
                     kahan_add(m10s[0], m10c[0], Ia.x); kahan_add(m10s[1], m10c[1], Ia.y);
                     if (hasb) { kahan_add(m10s[0], m10c[0], Ib.x); kahan_add(m10s[1], m10c[1], Ib.y); }
                 }
-                if (k * IT + tid == N) {   // u = (0, 1)
+                if (!FINE && k * IT + tid == N) {   // u = (0, 1)
                     kahan_add(m01s[0], m01c[0], Ia.x); kahan_add(m01s[1], m01c[1], Ia.y);
                     if (hasb) { kahan_add(m01s[0], m01c[0], Ib.x); kahan_add(m01s[1], m01c[1], Ib.y); }
                 }
@@ -246,6 +277,7 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
         }
         __syncthreads();
     }
+    if constexpr (FINE) return;
     // partial sums of this frame group, at the workgroup's index
     float *pp = ppart + (size_t)L * NP;
 #pragma unroll
@@ -260,7 +292,7 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
 }
 
 // The passes over a patch's frame-group partials (below) give every entry of
-// the stored half plane (rows 0..N/2) a thread of its own, FIN_PARTS
+// the stored half plane (rows 0..N/2) a thread of its own, PARTS
 // workgroups per patch: each thread waits for its few dependent sums once, and
 // even one patch spreads over several CUs.  (One workgroup per patch walked
 // the whole plane in a chain of 64 waits: 74 us for 12 patches of 6 groups, 5 now;
@@ -279,12 +311,61 @@ __device__ __forceinline__ int mirror_of(int j) {
     return uy >= 1 && uy < N / 2 ? (N - uy) * N + ((N - ux) & (N - 1)) : -1;
 }
 
+// The partial sums of frame group k of a patch: as k_ingest left them (its
+// first workgroup wg0), or (FINE) formed here from the records, rec0 the
+// patch's first, as k_ingest forms them.
+template <int N, bool FINE> struct Partials {
+    const float *ppart, *mpart, *mupart;
+    const float2 *spectra;
+    size_t wg0, rec0;
+    int chunk, F;
+    static constexpr size_t FS = SpecRows<N>::FS;
+    __device__ __forceinline__ float power(int k, int j) const {
+        if constexpr (!FINE) return ppart[(wg0 + k) * FinGeom<N>::NP + j];
+        const bool rec = j < N / 2 * N;
+        const int ux = j % N, m = ux <= N / 2 ? ux : N - ux;
+        const float2 *p = rec ? spectra + rec0 * FS + SPEC_NEG_ROWS * N + j
+                              : (const float2 *)(ppart + rec0 * fine_stride<N>()) + m;
+        const size_t step = rec ? FS : fine_stride<N>() / 2;
+        const int f0 = k * chunk, f1 = min(F, f0 + chunk);
+        float2 v[FINE_MAX_FRAMES];   // requested together (past the end: the last again, unused)
+#pragma unroll
+        for (int i = 0; i < FINE_MAX_FRAMES; ++i) v[i] = p[min(f0 + i, f1 - 1) * step];
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < FINE_MAX_FRAMES; ++i) s = f0 + i < f1 ? add_power(s, v[i]) : s;
+        return s;
+    }
+    // component c of I(1, 0), I(0, 1) as (re, im)
+    __device__ __forceinline__ float mean(int k, int c) const {
+        if constexpr (!FINE) return mpart[(wg0 + k) * 4 + c];
+        const float *p = (const float *)(spectra + rec0 * FS + SPEC_NEG_ROWS * N + (c < 2 ? 1 : N)) + (c & 1);
+        return group_sum(k, p, 2 * FS);
+    }
+    __device__ __forceinline__ float level(int k) const {
+        if constexpr (!FINE) return mupart[wg0 + k];
+        return group_sum(k, ppart + rec0 * fine_stride<N>() + N + 2, fine_stride<N>());
+    }
+    __device__ __forceinline__ float group_sum(int k, const float *p, size_t step) const {
+        const int f0 = k * chunk, f1 = min(F, f0 + chunk);
+        float v[FINE_MAX_FRAMES];
+#pragma unroll
+        for (int i = 0; i < FINE_MAX_FRAMES; ++i) v[i] = p[min(f0 + i, f1 - 1) * step];
+        float s = 0.f, c = 0.f;
+#pragma unroll
+        for (int i = 0; i < FINE_MAX_FRAMES; ++i)
+            if (f0 + i < f1) kahan_add(s, c, v[i]);
+        return s - c;
+    }
+};
+
 // Sums the frame groups (compensated) and divides by F.
-template <int N>
+template <int N, bool FINE>
 __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int chunk_frames,
                                                      const float *__restrict__ ppart,
                                                      const float *__restrict__ mpart,
                                                      const float *__restrict__ mupart,
+                                                     const float2 *__restrict__ spectra,
                                                      float *__restrict__ power, float *__restrict__ mean_spec,
                                                      float *__restrict__ mu) {
     constexpr int NP = FinGeom<N>::NP;
@@ -293,28 +374,30 @@ __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int ch
     const BurstDesc &bd = bt.b[b];
     const int nchunks = (bd.F + chunk_frames - 1) / chunk_frames;
     const float invF = 1.0f / (float)bd.F;
-    const size_t wg0 = (size_t)bd.ingest0 + (size_t)(patch - bd.patch0) * nchunks;   // its first ingest workgroup
+    const Partials<N, FINE> pt = {ppart, mpart, mupart, spectra,
+                                  (size_t)bd.ingest0 + (size_t)(patch - bd.patch0) * nchunks,
+                                  (size_t)bd.spec0 + (size_t)(patch - bd.patch0) * bd.F, chunk_frames, bd.F};
     const int j = part * NT + threadIdx.x;
     if (j < NP) {
-        const float *pp = ppart + wg0 * NP + j;
         float s = 0.f, c = 0.f;
-#pragma unroll 8
-        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, pp[(size_t)k * NP]);
+#pragma unroll FINE ? 1 : 8
+        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, pt.power(k, j));
         const float v = (s - c) * invF;
         float *pw = power + (size_t)patch * N * N;
         pw[j] = v;
         const int m = mirror_of<N>(j);
         if (m >= 0) pw[m] = v;
     }
-    if (part != 0) return;
-    if (threadIdx.x < 4) {
+    if (part != FinGeom<N>::PARTS - 1) return;   // (the part with the fewest entries)
+    const int i = threadIdx.x - (NT - 5);
+    if (i >= 0 && i < 4) {
         float s = 0.f, c = 0.f;
-        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, mpart[(wg0 + k) * 4 + threadIdx.x]);
-        mean_spec[(size_t)patch * 4 + threadIdx.x] = (s - c) * invF;
+        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, pt.mean(k, i));
+        mean_spec[(size_t)patch * 4 + i] = (s - c) * invF;
     }
-    if (threadIdx.x == 4) {
+    if (i == 4) {
         float s = 0.f, c = 0.f;
-        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, mupart[wg0 + k]);
+        for (int k = 0; k < nchunks; ++k) kahan_add(s, c, pt.level(k));
         mu[patch] = (s - c) * invF;
     }
 }
@@ -324,23 +407,26 @@ __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int ch
 // when first), sc = (sum, compensation) per value: power rows 0..N/2, the
 // two mean spectrum values and the mean level.  last != 0: then writes the
 // means over all frames, (sum - comp) * inv_total, as k_acc_finalize does.
-template <int N>
-__global__ __launch_bounds__(NT) void k_acc_stream(int nchunks, const float *__restrict__ ppart,
+template <int N, bool FINE>
+__global__ __launch_bounds__(NT) void k_acc_stream(int F, int chunk_frames, const float *__restrict__ ppart,
                                                    const float *__restrict__ mpart,
-                                                   const float *__restrict__ mupart, float2 *__restrict__ psc,
+                                                   const float *__restrict__ mupart,
+                                                   const float2 *__restrict__ spectra, float2 *__restrict__ psc,
                                                    float2 *__restrict__ msc, float2 *__restrict__ musc, int first,
                                                    int last,
                                                    float inv_total, float *__restrict__ power,
                                                    float *__restrict__ mean_spec, float *__restrict__ mu) {
     constexpr int NP = FinGeom<N>::NP;
     const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
+    const int nchunks = (F + chunk_frames - 1) / chunk_frames;
+    const Partials<N, FINE> pt = {ppart, mpart, mupart, spectra, (size_t)patch * nchunks, (size_t)patch * F,
+                                  chunk_frames, F};
     const int j = part * NT + threadIdx.x;
     if (j < NP) {
-        const float *pp = ppart + (size_t)patch * nchunks * NP + j;
         float2 *ps = psc + (size_t)patch * NP + j;
         float2 v = first ? make_float2(0.f, 0.f) : *ps;
-#pragma unroll 8
-        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, pp[(size_t)k * NP]);
+#pragma unroll FINE ? 1 : 8
+        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, pt.power(k, j));
         *ps = v;
         if (last) {
             float *pw = power + (size_t)patch * N * N;
@@ -350,44 +436,63 @@ __global__ __launch_bounds__(NT) void k_acc_stream(int nchunks, const float *__r
             if (mj >= 0) pw[mj] = m;
         }
     }
-    if (part != 0) return;
-    if (threadIdx.x < 4) {
-        float2 v = first ? make_float2(0.f, 0.f) : msc[(size_t)patch * 4 + threadIdx.x];
-        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, mpart[((size_t)patch * nchunks + k) * 4 + threadIdx.x]);
-        msc[(size_t)patch * 4 + threadIdx.x] = v;
-        if (last) mean_spec[(size_t)patch * 4 + threadIdx.x] = (v.x - v.y) * inv_total;
+    if (part != FinGeom<N>::PARTS - 1) return;
+    const int i = threadIdx.x - (NT - 5);
+    if (i >= 0 && i < 4) {
+        const size_t o = (size_t)patch * 4 + i;
+        float2 v = first ? make_float2(0.f, 0.f) : msc[o];
+        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, pt.mean(k, i));
+        msc[o] = v;
+        if (last) mean_spec[o] = (v.x - v.y) * inv_total;
     }
-    if (threadIdx.x == 4) {
+    if (i == 4) {
         float2 v = first ? make_float2(0.f, 0.f) : musc[patch];
-        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, mupart[(size_t)patch * nchunks + k]);
+        for (int k = 0; k < nchunks; ++k) kahan_add(v.x, v.y, pt.level(k));
         musc[patch] = v;
         if (last) mu[patch] = (v.x - v.y) * inv_total;
     }
 }
 
+template <int N, typename T, bool FINE>
+hipError_t launch_ingest_f(const IngestArgs &a, hipStream_t st) {
+    BurstTable bt = a.bt;
+    const int frames = FINE ? 2 : a.chunk_frames;
+    if (FINE) {   // one workgroup per frame pair
+        bt.ingest_wgs = 0;
+        for (int i = 0; i < bt.nb; ++i) {
+            const int patches = (i + 1 < bt.nb ? bt.b[i + 1].patch0 : bt.patches) - bt.b[i].patch0;
+            bt.b[i].ingest0 = bt.ingest_wgs;
+            bt.ingest_wgs += patches * ((bt.b[i].F + 1) / 2);
+        }
+    }
+    auto ingest = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(bt.ingest_wgs), dim3(ingest_threads<T>()), 0, st, bt, a.stride, frames,
+                           a.window, a.inv_wsum, a.twiddle, a.hann, a.spectra, a.ppart, a.mpart, a.mupart);
+        return hipGetLastError();
+    };
+    const hipError_t e = a.vec ? ingest(k_ingest<N, T, true, FINE>) : ingest(k_ingest<N, T, false, FINE>);
+    if (e != hipSuccess) return e;
+    const dim3 grid(a.bt.patches * FinGeom<N>::PARTS);
+    if (a.stream_mode == 0)
+        hipLaunchKernelGGL((k_acc_finalize<N, FINE>), grid, dim3(NT), 0, st, a.bt, a.chunk_frames, a.ppart, a.mpart,
+                           a.mupart, a.spectra, a.power, a.mean_spec, a.mu);
+    else
+        hipLaunchKernelGGL((k_acc_stream<N, FINE>), grid, dim3(NT), 0, st, a.bt.b[0].F, a.chunk_frames, a.ppart,
+                           a.mpart, a.mupart, a.spectra, a.psc, a.msc, a.musc, a.stream_first,
+                           a.stream_mode == 2 ? 1 : 0, a.inv_total, a.power, a.mean_spec, a.mu);
+    return hipGetLastError();
+}
+
 template <int N, typename T>
 hipError_t launch_ingest_t(const IngestArgs &a, hipStream_t st) {
-    if (a.vec)
-        hipLaunchKernelGGL((k_ingest<N, T, true>), dim3(a.bt.ingest_wgs), dim3(ingest_threads<T>()), 0, st, a.bt, a.stride,
-                           a.chunk_frames, a.window, a.inv_wsum, a.twiddle, a.hann, a.spectra, a.ppart, a.mpart,
-                           a.mupart);
-    else
-        hipLaunchKernelGGL((k_ingest<N, T, false>), dim3(a.bt.ingest_wgs), dim3(ingest_threads<T>()), 0, st, a.bt, a.stride,
-                           a.chunk_frames, a.window, a.inv_wsum, a.twiddle, a.hann, a.spectra, a.ppart, a.mpart,
-                           a.mupart);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (a.stream_mode == 0) {
-        hipLaunchKernelGGL((k_acc_finalize<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames,
-                           a.ppart, a.mpart, a.mupart, a.power, a.mean_spec, a.mu);
-    } else {
-        const int nchunks = (a.bt.b[0].F + a.chunk_frames - 1) / a.chunk_frames;
-        hipLaunchKernelGGL((k_acc_stream<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, nchunks, a.ppart, a.mpart,
-                           a.mupart, a.psc, a.msc, a.musc, a.stream_first, a.stream_mode == 2 ? 1 : 0, a.inv_total,
-                           a.power,
-                           a.mean_spec, a.mu);
+    // FINE needs room for its values in the partials of each frame's group,
+    // and groups of whole pairs
+    if constexpr (N >= 64) {
+        static_assert(FinGeom<N>::NP >= FINE_MAX_FRAMES * fine_stride<N>(), "fine values fit the partials");
+        if (a.bt.ingest_wgs <= FINE_MAX_WGS && a.chunk_frames <= FINE_MAX_FRAMES && a.chunk_frames % 2 == 0)
+            return launch_ingest_f<N, T, true>(a, st);
     }
-    return hipGetLastError();
+    return launch_ingest_f<N, T, false>(a, st);
 }
 
 // Photon-noise terms of one (patch, frame group), over the ingest grid.
