@@ -84,7 +84,7 @@ template <int N> struct FftGeom;
 template <> struct FftGeom<64> { static constexpr int R1 = 8, R2 = 8; };
 template <> struct FftGeom<128> { static constexpr int R1 = 8, R2 = 16; };
 
-// Storage position of frequency k after fft2d_lds (per axis).
+// Storage position of frequency k after fft2d_lds_inline (per axis).
 template <int N>
 __host__ __device__ constexpr int fft_pos(int k) {
     return FftGeom<N>::R1 * (k % FftGeom<N>::R2) + k / FftGeom<N>::R2;
@@ -107,20 +107,22 @@ template <int N> struct SpecRows {
 // exp(-2 pi i k / N).  Input in natural order; on return frequency
 // (ky, kx) sits at z[fft_pos(ky) * PITCH + fft_pos(kx)].  Each axis is a
 // radix-R2 pass over stride-R1 subsequences with twiddles, then a radix-R1
-// pass over contiguous groups.  Ends with a barrier.
-template <int N, int NT>
-__device__ __forceinline__ void fft2d_lds_inline(float2 *z, const float2 *tw) {
+// pass over contiguous groups.  Ends with a barrier.  BOX: the rows outside
+// [N/4, 3N/4) are zero, and the row passes leave them out.  tid: the thread's
+// index, for callers that keep it from the optimizer.
+template <int N, int NT, bool BOX = false>
+__device__ __forceinline__ void fft2d_lds_inline(float2 *z, const float2 *tw, int tid = threadIdx.x) {
     constexpr int R1 = FftGeom<N>::R1, R2 = FftGeom<N>::R2, P = LdsPitch<N>::v;
-    const int tid = threadIdx.x;
     // axis 0 = along x (rows), axis 1 = along y (columns)
 #pragma unroll
     for (int axis = 0; axis < 2; ++axis) {
         const int es = axis == 0 ? 1 : P;   // element step along the axis
         const int ls = axis == 0 ? P : 1;   // step between lines
+        const int nl = BOX && axis == 0 ? N / 2 : N, l0 = BOX && axis == 0 ? N / 4 : 0;   // lines
         // pass A: for each line and n1, DFT over n2 of x[n1 + R1 n2]
 #pragma unroll 2
-        for (int t = tid; t < N * R1; t += NT) {
-            const int line = t % N, n1 = t / N;
+        for (int t = tid; t < nl * R1; t += NT) {
+            const int line = l0 + t % nl, n1 = t / nl;
             float2 v[R2];
             float2 *base = z + line * ls + n1 * es;
 #pragma unroll
@@ -135,8 +137,8 @@ __device__ __forceinline__ void fft2d_lds_inline(float2 *z, const float2 *tw) {
         __syncthreads();
         // pass B: for each line and k2, DFT over n1 of the contiguous group
 #pragma unroll 2
-        for (int t = tid; t < N * R2; t += NT) {
-            const int line = t % N, k2 = t / N;
+        for (int t = tid; t < nl * R2; t += NT) {
+            const int line = l0 + t % nl, k2 = t / nl;
             float2 v[R1];
             float2 *base = z + line * ls + (R1 * k2) * es;
 #pragma unroll
@@ -147,12 +149,6 @@ __device__ __forceinline__ void fft2d_lds_inline(float2 *z, const float2 *tw) {
         }
         __syncthreads();
     }
-}
-// The same, left to the compiler to inline or call (a call keeps the
-// transform's registers out of a caller that holds many of its own).
-template <int N, int NT>
-__device__ void fft2d_lds(float2 *z, const float2 *tw) {
-    fft2d_lds_inline<N, NT>(z, tw);
 }
 
 // A wave-uniform pointer held in scalar registers, opaque to the optimizer:

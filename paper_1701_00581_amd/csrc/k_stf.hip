@@ -18,9 +18,13 @@
 // accumulated over the half plane of frequencies.  The second screen's
 // phases over the pupil's bounding box wait in LDS while the first screen
 // is used.
-// The transforms leave their output in the storage order of fft2d_lds;
-// element-wise steps work there, and each thread moves its pixels back to
-// natural order through registers before the next transform.
+// The transforms leave their output in the storage order of fft2d_lds_inline;
+// each thread moves its pixels back to natural order through registers
+// before the next transform.  Only the pupil's bounding box, a quarter of the
+// grid, holds phases that are used: the subharmonics and the fields are formed
+// there alone, and the field's transform leaves out the zero rows.
+// Bound by LDS (the transforms, 5 per pair) and issue at one workgroup per CU:
+// 1000 screens at N = 128 in 208 -> 137 us.
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -30,7 +34,9 @@ namespace nvsm {
 
 namespace {
 
-constexpr int ST = 512;
+// Threads of a workgroup: the N = 128 tile fills a CU's LDS, so a workgroup
+// has to bring all the waves that hide one another's waits.
+template <int N> constexpr int stf_threads() { return N == 128 ? 1024 : 512; }
 
 __device__ __forceinline__ void philox4x32_10(uint32_t (&c)[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -74,9 +80,10 @@ __device__ __forceinline__ void sub_offset(int k, int &iy, int &ix) {
 }
 
 template <int N>
-__global__ __launch_bounds__(ST) void k_stf(int pairs, float amp, const double *__restrict__ x_dev, uint32_t k0,
+__global__ __launch_bounds__(stf_threads<N>()) void k_stf(int pairs, float amp, const double *__restrict__ x_dev, uint32_t k0,
                                             uint32_t k1, uint32_t stream, const float2 *__restrict__ twiddle,
                                             float2 *__restrict__ part_a, float *__restrict__ part_s) {
+    constexpr int ST = stf_threads<N>();
     constexpr int P = LdsPitch<N>::v;
     constexpr int NP = (N / 2 + 1) * N;           // half plane: rows 0..N/2
     constexpr int PX = N * N / ST;                // pixels per thread
@@ -86,6 +93,7 @@ __global__ __launch_bounds__(ST) void k_stf(int pairs, float amp, const double *
     __shared__ float2 sh[24];                     // subharmonic coefficients
     __shared__ float2 sct[3][N];                  // (cos, sin)(2 pi t / (N 3^p)), t = 0 .. N - 1
     constexpr int PB = N / 2, PB0 = N / 4;        // the pupil's bounding box: [PB0, PB0 + PB)^2
+    constexpr int BX = PB * PB / ST;              // its pixels per thread
     __shared__ float side[PB * PB];               // the second screen's phases over that box
     const int tid = threadIdx.x;
     for (int i = tid; i < N; i += ST) tw[i] = twiddle[i];
@@ -117,13 +125,21 @@ __global__ __launch_bounds__(ST) void k_stf(int pairs, float amp, const double *
         return dx * dx + dy * dy <= PUPIL_R2;
     };
 
-    // storage position -> natural index along one axis of the transform
-    auto nat = [](int p) { return (p % FftGeom<N>::R1) * FftGeom<N>::R2 + p / FftGeom<N>::R1; };
     // A pair's screens are the real and imaginary parts of one transform:
     // the first screen's field goes to registers, the second screen's
     // phases inside the pupil to the side buffer, until its turn.
+    // The thread's index, opaque at each step: the steps' addresses are then
+    // formed where they are used instead of all being held through the loop,
+    // which took more registers than 16 waves have.
+    auto lane = [&]() __attribute__((always_inline)) {
+        int t;
+        asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(threadIdx.x));
+        __builtin_assume(t >= 0 && t < ST);
+        return t;
+    };
     for (int j = blockIdx.x; j < pairs; j += gridDim.x) {
         {
+            const int tid = lane();
             __syncthreads();                       // previous use of z, sh and side done
             // spectrum of the screen pair, natural order
 #pragma unroll 1
@@ -157,13 +173,17 @@ __global__ __launch_bounds__(ST) void k_stf(int pairs, float amp, const double *
                 }
             }
             __syncthreads();
-            fft2d_lds<N, ST>(z, tw);
-            // subharmonics, in place at each stored position
-#pragma unroll 1
-            for (int i = tid; i < N * N; i += ST) {
-                const int row = i / N, col = i % N;
-                const int y = nat(row), x = nat(col);
-                float2 v = z[row * P + col];
+            fft2d_lds_inline<N, ST>(z, tw, lane());
+        }
+        // the phases inside the pupil: plus the subharmonics; the first
+        // screen's field, and the second screen's phases to the side buffer
+        float2 t[BX];
+#pragma unroll
+        for (int k = 0; k < BX; ++k) {
+            const int b = k * ST + lane(), y = PB0 + b / PB, x = PB0 + b % PB;
+            float s = 0.f, c = 0.f;
+            if (in_pupil(y, x)) {
+                float2 v = z[fft_pos<N>(y) * P + fft_pos<N>(x)];
 #pragma unroll
                 for (int p = 1; p <= 3; ++p) {
                     // exp(2 pi i x / (N 3^p)) and the same for y
@@ -181,21 +201,8 @@ __global__ __launch_bounds__(ST) void k_stf(int pairs, float amp, const double *
                         v.y += c.x * ei + c.y * er;
                     }
                 }
-                z[row * P + col] = v;
-            }
-            __syncthreads();
-        }
-        // field = pupil exp(i phi) of the first screen, to natural order; the
-        // second screen's phases to the side buffer
-        float2 t[PX];
-#pragma unroll
-        for (int k = 0; k < PX; ++k) {
-            const int e = k * ST + tid, y = e / N, x = e % N;
-            float s = 0.f, c = 0.f;
-            if (in_pupil(y, x)) {
-                const float2 v = z[fft_pos<N>(y) * P + fft_pos<N>(x)];
                 sincosf(v.x, &s, &c);
-                side[(y - PB0) * PB + (x - PB0)] = v.y;
+                side[b] = v.y;
             }
             t[k] = make_float2(c, s);
         }
@@ -205,23 +212,31 @@ __global__ __launch_bounds__(ST) void k_stf(int pairs, float amp, const double *
         for (int scr = 0; scr < 2; ++scr) {
             if (scr) {
 #pragma unroll
-                for (int k = 0; k < PX; ++k) {
-                    const int e = k * ST + tid, y = e / N, x = e % N;
+                for (int k = 0; k < BX; ++k) {
+                    const int b = k * ST + lane();
                     float s = 0.f, c = 0.f;
-                    if (in_pupil(y, x)) sincosf(side[(y - PB0) * PB + (x - PB0)], &s, &c);
+                    if (in_pupil(PB0 + b / PB, PB0 + b % PB)) sincosf(side[b], &s, &c);
                     t[k] = make_float2(c, s);
                 }
             }
             __syncthreads();                       // the transform (or the last OTF) was read
 #pragma unroll
-            for (int k = 0; k < PX; ++k) {
-                const int e = k * ST + tid;
-                z[(e / N) * P + e % N] = t[k];
+            for (int k = 0; k < BX; ++k) {
+                const int b = k * ST + lane();
+                z[(PB0 + b / PB) * P + PB0 + b % PB] = t[k];
+                // the zeros around the box (not folded into the transform: its sums
+                // then fuse with other products, and the last bits change)
+                const int y = b / PB, x = b % PB;
+                z[(PB0 + y) * P + (x < PB0 ? x : x + PB)] = make_float2(0.f, 0.f);
+#pragma unroll
+                for (int h = 0; h < N; h += PB)
+                    z[(y < PB0 ? y : y + PB) * P + x + h] = make_float2(0.f, 0.f);
             }
             __syncthreads();
-            fft2d_lds<N, ST>(z, tw);
+            fft2d_lds_inline<N, ST, true>(z, tw, lane());
             // PSF = |.|^2, to natural order for the next transform
             float psf[PX];
+            const int tid = lane();
 #pragma unroll
             for (int k = 0; k < PX; ++k) {
                 const int e = k * ST + tid, y = e / N, x = e % N;
@@ -235,12 +250,11 @@ __global__ __launch_bounds__(ST) void k_stf(int pairs, float amp, const double *
                 z[(e / N) * P + e % N] = make_float2(psf[k], 0.f);
             }
             __syncthreads();
-            fft2d_lds<N, ST>(z, tw);
+            fft2d_lds_inline<N, ST>(z, tw, lane());
             const float o0 = z[0].x;               // OTF(0) = sum of the PSF
 #pragma unroll 4
-            for (int q = tid; q < NP; q += ST) {
-                const int uy = q / N, ux = q % N;
-                const float2 o = z[fft_pos<N>(uy) * P + fft_pos<N>(ux)];
+            for (int q = lane(); q < NP; q += ST) {
+                const float2 o = z[fft_pos<N>(q / N) * P + q % N];   // (columns in storage order)
                 const float ox = o.x / o0, oy = o.y / o0;    // (a division: exactly 1 at u = 0)
                 const float2 a = pa[q];
                 pa[q] = make_float2(a.x + ox, a.y + oy);
@@ -290,7 +304,8 @@ __global__ __launch_bounds__(256) void k_stf_finalize(int nwg, double inv_screen
     ax *= inv_screens;
     ay *= inv_screens;
     s *= inv_screens;
-    const int uy = q / N, ux = q % N;
+    // the partials' columns are in the transform's storage order
+    const int uy = q / N, ux = (q % FftGeom<N>::R1) * FftGeom<N>::R2 + q % N / FftGeom<N>::R1;
     stf[uy * N + ux] = s;
     if (mean_otf) mean_otf[uy * N + ux] = make_double2(ax, ay);
     if (uy >= 1 && uy < N / 2) {
@@ -302,7 +317,7 @@ __global__ __launch_bounds__(256) void k_stf_finalize(int nwg, double inv_screen
 
 template <int N>
 hipError_t launch_stf_t(const StfArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL((k_stf<N>), dim3(a.nwg), dim3(ST), 0, st, a.pairs, a.amp, a.x_dev, a.k0, a.k1, a.stream,
+    hipLaunchKernelGGL((k_stf<N>), dim3(a.nwg), dim3(stf_threads<N>()), 0, st, a.pairs, a.amp, a.x_dev, a.k0, a.k1, a.stream,
                        a.twiddle, a.part_a, a.part_s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
