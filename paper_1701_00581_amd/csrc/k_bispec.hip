@@ -10,17 +10,7 @@
 //   * each lane loads its own I(w), and lane l the slot value I(v) of slot
 //     l mod 16, into registers; a slot's value reaches every lane through a
 //     DPP row broadcast folded into the multiplies that use it.
-// Each slot then costs one 64-bit LDS gather and 7 FP32 FMA/MUL per lane.
-// The loop is bound by VALU issue (0.88 of the cycles, and the clock falls
-// with the power it draws), so a slot's product is formed in three
-// instructions instead of four: with I(w) = c + i d and I(v) = x + i y,
-//   m = c (x + y),  I(v) conj I(w) = (m - y (c - d)) + i (m - x (c + d)),
-// the sums c -+ d and x + y formed once per frame.  m is needed twice, and a
-// DPP multiply-add overwrites its addend, so y comes as a scalar (one scalar
-// load per slot and frame, issued after the slot loop): the first use of m is
-// then a three-operand FMA.  45.4 -> 43.0 ms for 1287 patches of 100 frames
-// at N = 128, R = 12, both on one machine; against the FP64 values the error
-// of the mean is unchanged (2.5e-7 normwise: that of the spectra).
+// Each slot then costs one 64-bit LDS gather and 8 FP32 FMA/MUL per lane.
 // LDS bandwidth is the other limit of this loop (a 64-bit read returns 16
 // lanes per clock), so I(v) and I(w) stay out of LDS and the lanes of a
 // group are laid out for conflict-free gathers (see plan.cpp).
@@ -50,15 +40,13 @@ template <int K> struct Region {
 };
 
 typedef __attribute__((address_space(3))) void *lds_ptr;
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-// scalar buffer load (wave-uniform descriptor and offset) of one dword
-__device__ float s_buffer_load_f32(i32x4 rsrc, int offset, int cache) __asm("llvm.amdgcn.s.buffer.load.f32");
 typedef unsigned u32x2 __attribute__((__vector_size__(2 * sizeof(unsigned))));
 
 __device__ __forceinline__ float2 as_f2(u32x2 v) { return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1])); }
 
-// b taken from lane K of this lane's row of 16 (DPP row_newbcast), times a;
-// and acc - that product.  Arithmetic only; EXEC must be full.
+// b taken from lane K of this lane's row of 16 (DPP row_newbcast), times a
+// (negated, for mul_bc_neg); and acc + that product.  Arithmetic only; EXEC
+// must be full.
 template <int K>
 __device__ __forceinline__ float mul_bc(float b, float a) {
     float r;
@@ -67,19 +55,17 @@ __device__ __forceinline__ float mul_bc(float b, float a) {
     return r;
 }
 template <int K>
-__device__ __forceinline__ float fmac_bc_neg(float acc, float b, float a) {
-    asm("v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+__device__ __forceinline__ float mul_bc_neg(float b, float a) {
+    float r;
+    asm("v_mul_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "=v"(r) : "v"(b), "v"(a), "i"(K));
+    return r;
+}
+template <int K>
+__device__ __forceinline__ float fmac_bc(float acc, float b, float a) {
+    asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf bound_ctrl:1"
         : "+v"(acc) : "v"(b), "v"(a), "i"(K));
     return acc;
-}
-
-// a + b as a broadcast source: a DPP read needs two wait states after the
-// VALU write of its source, which the compiler does not insert before the
-// asm above.
-__device__ __forceinline__ float add_for_bc(float a, float b) {
-    float r;
-    asm("v_add_f32 %0, %1, %2\n\ts_nop 1" : "=v"(r) : "v"(a), "v"(b));
-    return r;
 }
 
 // Compensated (Kahan) fold of the block sum t into s.  The rounding error
@@ -142,12 +128,6 @@ __device__ __forceinline__ void bispec_item(float2 *lds0, float2 *lds1, const fl
     int addr[NS];     // LDS byte offset of I(w - v) in the region, per slot
 #pragma unroll
     for (int k = 0; k < NS; ++k) addr[k] = (lane_base - sl[2 * k]) * (int)sizeof(float2);
-    int so[NS];       // byte offset of Im I(v) in a frame's record, per slot (wave-uniform)
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        so[k] = sl[2 * k + 1] * (int)sizeof(float2) + 4;
-        asm("" : "+s"(so[k]));
-    }
     int sol[NQ];      // byte offset of I(v) of slot 16 q + lane mod 16 in a frame's record
 #pragma unroll
     for (int q = 0; q < NQ; ++q) sol[q] = sl[2 * min(16 * q + (lane & 15), K - 1) + 1] * (int)sizeof(float2);
@@ -176,32 +156,27 @@ __device__ __forceinline__ void bispec_item(float2 *lds0, float2 *lds1, const fl
         src[j] = (unsigned)(o * (int)sizeof(float2));
     }
 
-    // each frame's record is a buffer of its own: loads add no frame offset
-    const char *sp = (const char *)(spec + (size_t)rec0 * FS);
+    // the patch's spectra as one buffer resource; frame f at byte f * FB
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(spec + (size_t)rec0 * FS), (short)0, F * FB, 0x00020000);
     // With the photon-noise terms, the last frame stages the same region of
     // the patch's C table (record layout) instead of a spare copy of itself,
     // so that the correction reads C(w - v) from LDS at the slots' offsets.
     const bool photon = MODE == 2 || (MODE == 1 && acc.noise_c != nullptr);
+    const __amdgpu_buffer_rsrc_t rsrc_c = __builtin_amdgcn_make_buffer_rsrc(
+        photon ? (void *)(acc.noise_c + (size_t)patch * FS) : (void *)spec, (short)0, photon ? FB : 0, 0x00020000);
     // the region loads of frame f into buf (f = F: the C table's region)
     auto fetch = [&](int f, float2 *buf) __attribute__((always_inline)) {
-        const char *src_f = sp + (size_t)((unsigned)f * (unsigned)FB);
-        if (photon && f == F) src_f = (const char *)(acc.noise_c + (size_t)patch * FS);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)src_f, (short)0, FB, 0x00020000);
+        const bool c = photon && f == F;
 #pragma unroll
         for (int j = 0; j < PERW; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(buf + 128 * (wave + BS_WAVES * j)), 16, (int)src[j], 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(c ? rsrc_c : rsrc, (lds_ptr)(buf + 128 * (wave + BS_WAVES * j)), 16,
+                                                     (int)src[j], c ? 0 : f * FB, 0, 0);
     };
-    // I(w), the slot values of the DPP rows, and the slots' Im I(v) as
-    // wave-uniform scalars
-    auto load_vals = [&](int f, float2 &cw, float2 (&bv)[NQ], float (&bi)[NS]) __attribute__((always_inline)) {
-        const char *src_f = sp + (size_t)((unsigned)f * (unsigned)FB);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)src_f, (short)0, FB, 0x00020000);
-        const i32x4 rf = {(int)(unsigned long long)src_f, (int)((unsigned long long)src_f >> 32), FB, 0x00020000};
+    auto load_vals = [&](int f, float2 &cw, float2 (&bv)[NQ]) __attribute__((always_inline)) {
+        cw = as_f2(__builtin_amdgcn_raw_buffer_load_b64(rsrc, wo, f * FB, 0));
 #pragma unroll
-        for (int k = 0; k < NS; ++k) bi[k] = s_buffer_load_f32(rf, so[k], 0);
-        cw = as_f2(__builtin_amdgcn_raw_buffer_load_b64(rs, wo, 0, 0));
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) bv[q] = as_f2(__builtin_amdgcn_raw_buffer_load_b64(rs, sol[q], 0, 0));
+        for (int q = 0; q < NQ; ++q) bv[q] = as_f2(__builtin_amdgcn_raw_buffer_load_b64(rsrc, sol[q], f * FB, 0));
     };
 
     // running sums of earlier frame groups, in this launch's lane order:
@@ -226,9 +201,8 @@ __device__ __forceinline__ void bispec_item(float2 *lds0, float2 *lds1, const fl
     }
 
     float2 cw, bv[NQ];
-    float bi[NS];
     fetch(0, lds0);
-    load_vals(0, cw, bv, bi);
+    load_vals(0, cw, bv);
     wait_vm<0>();
     __builtin_amdgcn_s_barrier();
 
@@ -244,23 +218,18 @@ __device__ __forceinline__ void bispec_item(float2 *lds0, float2 *lds1, const fl
         const int fn = min(f + 1, F - 1);
         fetch(photon ? f + 1 : fn, nxt);
         const char *rb = (const char *)rg;
-        // q = I(v) conj I(w);  t += I(w - v) q.  The gather of slot k + 1 is
+        // p = I(w - v) I(v);  t += p conj I(w).  The gather of slot k + 1 is
         // requested before slot k is computed, so that its LDS latency runs
         // under slot k's arithmetic.
-        const float cd = cw.x - cw.y, cs = cw.x + cw.y;
-        float bs[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) bs[q] = add_for_bc(bv[q].x, bv[q].y);
         float2 an = *(const float2 *)(rb + addr[0]);
         auto slot_k = [&](auto kc) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value, q = k / 16, r = k % 16;
             const float2 a = an;
             if constexpr (k + 1 < NS) an = *(const float2 *)(rb + addr[k + 1]);
-            const float m = mul_bc<r>(bs[q], cw.x);
-            const float qr = fmaf(-bi[k], cd, m);
-            const float qi = fmac_bc_neg<r>(m, bv[q].x, cs);
-            t[k].x = fmaf(a.x, qr, fmaf(-a.y, qi, t[k].x));
-            t[k].y = fmaf(a.x, qi, fmaf(a.y, qr, t[k].y));
+            const float pr = fmac_bc<r>(mul_bc_neg<r>(bv[q].y, a.y), bv[q].x, a.x);
+            const float pi = fmac_bc<r>(mul_bc<r>(bv[q].x, a.y), bv[q].y, a.x);
+            t[k].x = fmaf(pr, cw.x, fmaf(pi, cw.y, t[k].x));
+            t[k].y = fmaf(pi, cw.x, fmaf(pr, -cw.y, t[k].y));
         };
         static_for<NS>(slot_k);
         if ((f + 1) % KB == 0 || f + 1 == F) {
@@ -270,10 +239,9 @@ __device__ __forceinline__ void bispec_item(float2 *lds0, float2 *lds1, const fl
                 fold_carry(s[k].y, t[k].y);
             }
         }
-        // (before the scalar loads: LDS reads and scalar loads share a counter)
-        wait_lds();
-        load_vals(fn, cw, bv, bi);
+        load_vals(fn, cw, bv);
         wait_vm<1 + NQ>();
+        wait_lds();
         __builtin_amdgcn_s_barrier();
     };
 
@@ -397,13 +365,13 @@ __device__ __forceinline__ int item_at(const BurstTable &bt, int o, int n_items)
 // Waves per SIMD the kernel is built for.  With 16 slots it fits 96 VGPRs
 // (two accumulators per slot value, 16 LDS offsets), i.e. 5 waves per
 // SIMD; more waves hide more of the latency of the one LDS gather each slot
-// waits for (measured with 8 instructions per slot: 51.7 ms at 5 waves
-// against 53.6 ms at 4).  A few values are spilled around the frame loop,
-// none inside it.  The streaming form needs 101 VGPRs without spills and is
-// bound by its running sums: 4 waves 2.10, 5 waves 2.17 ms per group of 20
-// frames of 225 patches (R = 10).  The persistent form (k_bispec_queue)
-// needs about 104 VGPRs and runs at 4.
-constexpr int bs_waves_per_eu(int K, int MODE) { return K <= 16 ? (MODE != 1 ? 5 : 4) : 2; }
+// waits for (measured: 51.7 ms at 5 waves against 53.6 ms at 4 with 97
+// VGPRs, and 52.5 ms at 4 with all 16 gathers of a frame issued ahead; at 5
+// waves a second gather in flight gains nothing).
+// The photon form then keeps one 8-byte value in scratch across the frame
+// loop (stored before it, reloaded after).  The persistent form
+// (k_bispec_queue) needs about 100 VGPRs and runs at 4.
+constexpr int bs_waves_per_eu(int K) { return K <= 16 ? 5 : 2; }
 
 // One workgroup per item.  MODE 0 writes the mean of all frames; MODE 1
 // adds a frame group to the running sums of acc (acc.mode 1 and 2); MODE 2
@@ -411,7 +379,7 @@ constexpr int bs_waves_per_eu(int K, int MODE) { return K <= 16 ? (MODE != 1 ? 5
 // is a separate instantiation, so that the plain form carries none of the
 // others' registers.
 template <int N, int K, int MODE>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(bs_waves_per_eu(K, MODE)))) void k_bispec(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(bs_waves_per_eu(K)))) void k_bispec(
     const BurstTable bt, const float2 *__restrict__ spec, int n_items, int total, const int *__restrict__ items,
     const int *__restrict__ group_xy, const int *__restrict__ slot, const int *__restrict__ out_idx,
     float2 *__restrict__ bispec, int64_t s_count, const AccState acc) {
