@@ -56,8 +56,17 @@ template <typename T> struct Quad<T, false> {
     __device__ float operator[](int i) const { return e[i]; }
 };
 
-// s + |I|^2
-__device__ __forceinline__ float add_power(float s, float2 I) { return fmaf(I.x, I.x, fmaf(I.y, I.y, s)); }
+// s + |I|^2, I the first (B false) or second frame of a pair.  |I|^2 is formed
+// before it is added, so that the sum over frames is rounded once a frame; the
+// order of the parts is fixed per frame of a pair so that every pass that forms
+// these sums gets the same bits.  (Both parts multiplied into the sum round it
+// twice: 6.3e-8 -> 8.5e-8 rms for the mean of 16 frames, of the same spectra.)
+template <bool B>
+__device__ __forceinline__ float add_power(float s, float2 I) {
+#pragma clang fp contract(off)
+    const float p = B ? fmaf(I.y, I.y, I.x * I.x) : fmaf(I.x, I.x, I.y * I.y);
+    return s + p;
+}
 
 // Storage position of frequency k after the transform (as fft_pos), in
 // unsigned arithmetic for indices the optimizer cannot bound.
@@ -243,8 +252,8 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
                 float2 Ia, Ib;
                 split(ux, uy, Ia, Ib);
                 if constexpr (!FINE) {
-                    ps[k] = add_power(ps[k], Ia);
-                    if (hasb) ps[k] = add_power(ps[k], Ib);
+                    ps[k] = add_power<false>(ps[k], Ia);
+                    if (hasb) ps[k] = add_power<true>(ps[k], Ib);
                 } else if (k * IT >= HALF * N && ux <= HALF) {
                     fine_a[ux] = Ia;
                     if (hasb) fine_b[ux] = Ib;
@@ -333,7 +342,8 @@ template <int N, bool FINE> struct Partials {
         for (int i = 0; i < FINE_MAX_FRAMES; ++i) v[i] = p[min(f0 + i, f1 - 1) * step];
         float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < FINE_MAX_FRAMES; ++i) s = f0 + i < f1 ? add_power(s, v[i]) : s;
+        for (int i = 0; i < FINE_MAX_FRAMES; ++i)   // (groups are whole pairs)
+            if (f0 + i < f1) s = i % 2 ? add_power<true>(s, v[i]) : add_power<false>(s, v[i]);
         return s;
     }
     // component c of I(1, 0), I(0, 1) as (re, im)
