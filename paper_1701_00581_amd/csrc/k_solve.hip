@@ -107,7 +107,7 @@ struct UnitRegs {
 };
 
 template <int N, int TPL, int BIG>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6 : 2))) void k_solve(int base, int nW, int n_units, const int *__restrict__ units,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6 : 2))) void k_solve(int nW, int n_units, const int *__restrict__ units,
                                               int zero_slot, const unsigned *__restrict__ code,
                                               const int *__restrict__ Wxy, const float *__restrict__ power,
                                               const float *__restrict__ mean_spec,
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6
                                               double *__restrict__ amp, double2 *__restrict__ phasor) {
     __shared__ double2 e[Win<BIG>::INNER + Win<BIG>::RING + 1];   // + the zero phasor
     __shared__ double red[NWAVE];
-    const int patch = base + blockIdx.x;
+    const int patch = blockIdx.x;
     const double *stf = bt.b[burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; })].stf;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -280,36 +280,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6
     }
 }
 
-// The modulus and phase of one patch per workgroup, in steps, for bursts of
-// few patches (see PHASE_MAX_PATCHES) and v radii of at most PH_MAX_PAIRS
-// pairs +-v (R <= 12); k_solve takes the others.
-//
-// The recursion is a chain of about 960 dependent groups of shells per patch
-// (N = 128), and k_solve pays for every link the whole of a unit's work: the
-// loads, two scattered LDS gathers per sample, the 64-lane sums and the
-// root, 0.8 us a link.  But of a w's up to 214 samples only a few (8 at most,
-// 2.6 on average) read a phasor of the two steps before.  So the waves have
-// roles:
-//   bulk waves (two w of the next step each, one per half wave) sum the
-//     bulk of step s + 1, from phasors gathered during the step before, and
-//     gather those of step s + 2;
-//   the critical wave (8 lanes per w, one fresh sample each) meanwhile adds
-//     the fresh samples of step s to the bulk sums the step before left in
-//     LDS, takes the root and writes the phasors.
-// A step then costs one short LDS - sum - root - LDS chain and one barrier.
-// A bulk lane keeps the phasors of its pairs +-v (a w has at most one of each
-// pair, the one on its side of the origin) in registers, so a sample costs
-// one LDS gather, on a raster of the plane where neighbouring lanes read
-// neighbouring entries.  Codes are loaded RING - 1 steps ahead and the samples
-// they place AHEAD steps ahead.
-// A step takes 0.49 us: the bulk waves issue for 1130 of its 1190 clocks (a
-// vector load holds its wave for about 43 clocks, an LDS gather for 24, a
-// sample's arithmetic for 77), the critical wave for 650.  Fewer, wider
-// loads and one sample's loads between the next samples' arithmetic took it
-// from 0.57; the memory's latency is not in it (the same with every load from
-// one 4 KB window).
-// The raster (154 KB at N = 128, R = 12) allows one workgroup per CU there,
-// whose 8 waves then have 256 registers each.
 // n consecutive words at byte offset off of r (n 1..4)
 template <int n>
 __device__ __forceinline__ void load_words(const __amdgpu_buffer_rsrc_t r, unsigned off, unsigned *w) {
@@ -339,9 +309,44 @@ struct PhaseArgs {
     const int *vslot;
 };
 
+// The modulus and phase of one patch per workgroup, in steps, where that is at
+// least as fast for any number of patches (plan.cpp, solve_in_steps: two pairs
+// +-v per lane at N = 64, R = 10 with u_cut >= 60 at N = 128); k_solve takes
+// the others.
+//
+// The recursion is a chain of dependent groups of shells per patch (942 at
+// N = 128, R = 10), and k_solve pays for every link the whole of a unit's work:
+// the loads, two scattered LDS gathers per sample, the 64-lane sums and the
+// root, 0.7 us a link.  But of a w's up to 155 samples only a few (8 at most,
+// 2.0 on average) read a phasor of the two steps before.  So the waves have
+// roles:
+//   bulk waves (two w of the next step each, one per half wave) sum the
+//     bulk of step s + 1, from phasors gathered during the step before, and
+//     gather those of step s + 2;
+//   the critical wave (8 lanes per w, one fresh sample each) meanwhile adds
+//     the fresh samples of step s to the bulk sums the step before left in
+//     LDS, takes the root and writes the phasors.
+// A step then costs one short LDS - sum - root - LDS chain and one barrier.
+// A bulk lane keeps the phasors of its pairs +-v (a w has at most one of each
+// pair, the one on its side of the origin) in registers, so a sample costs
+// one LDS gather, on a raster of the plane where neighbouring lanes read
+// neighbouring entries.  Codes are loaded RING - 1 steps ahead and the samples
+// they place AHEAD steps ahead.
+// The 1094 steps at N = 128, R = 10 take 0.49 us each: a vector load holds a
+// bulk wave for about 43 clocks, an LDS gather for 24, a sample's arithmetic
+// for 77, together about 1130 of a step's 1190 clocks.  Fewer, wider loads and
+// one sample's loads between the next samples' arithmetic took it from 0.57;
+// the memory's latency is not in it (the same with every load from one 4 KB
+// window).
+// The raster (154 KB at N = 128) allows one workgroup per CU there, whose 8
+// waves then have 256 registers each; at N = 64 (45 KB, two pairs per lane in 76
+// registers) a CU holds three.  Waves past the bulk waves share the set-up and
+// end; workgroups of the recursion's five waves alone load the four SIMDs
+// unevenly (N = 64, R = 6, 1024 patches: 344 us with k_solve, 367 with five
+// waves, 277 with eight).
 template <int N, int TPL>
-__global__ __launch_bounds__(PH_NT) __attribute__((amdgpu_waves_per_eu(N == 128 ? 2 : TPL <= 4 ? 4 : 2))) void k_phase(
-    int base, int nW, const PhaseArgs pa, const int *__restrict__ Wxy, const float *__restrict__ power,
+__global__ __launch_bounds__(PH_NT) __attribute__((amdgpu_waves_per_eu(N == 128 ? 2 : 6))) void k_phase(
+    int nW, const PhaseArgs pa, const int *__restrict__ Wxy, const float *__restrict__ power,
     const float *__restrict__ mean_spec, const float2 *__restrict__ bispec, const BurstTable bt, double floor_,
     int noise_bias, double *__restrict__ amp, double2 *__restrict__ phasor) {
     constexpr int PWAVES = PH_NT / 64;
@@ -350,7 +355,7 @@ __global__ __launch_bounds__(PH_NT) __attribute__((amdgpu_waves_per_eu(N == 128 
     __shared__ double2 e[ph_entries_max<N>()];
     __shared__ double zb[2][PH_WIDE][2];         // bulk sums of the step to be finished
     __shared__ double red[2][PWAVES];
-    const int patch = base + blockIdx.x;
+    const int patch = blockIdx.x;
     const double *stf = bt.b[burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; })].stf;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -784,14 +789,6 @@ __global__ __launch_bounds__(LSQ_NT) void k_lsq(int nW, int n_inner, int iters, 
     }
 }
 
-template <int N, int TPL, int BIG>
-hipError_t launch_solve_t(const SolveArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL((k_solve<N, TPL, BIG>), dim3(a.bt.patches), dim3(NT), 0, st, a.nW, a.n_units, a.units,
-                       a.zero_slot, a.code, a.Wxy, a.power, a.mean_spec, a.bispec,
-                       a.s_count, a.bt, a.floor, a.noise_bias, a.amp, a.phasor);
-    return hipGetLastError();
-}
-
 // The same steps with one w per wave and the pairs +-v over its lanes (at
 // most LSQ_MAX_PAIRS pairs, R <= 12; k_lsq takes the others): a w has at most
 // one sample of each pair, so lane l always meets the same TPL pairs.  Their
@@ -990,54 +987,31 @@ __global__ __launch_bounds__(LQ_NT) void k_lsq_pairs(int nW, int n_inner, int it
 }
 
 template <int N, int TPL>
-hipError_t launch_phase_t(const SolveArgs &a, int base, int patches, hipStream_t st) {
+hipError_t launch_phase_t(const SolveArgs &a, hipStream_t st) {
     const PhaseArgs pa = {a.ph_steps, a.ph_early, a.ph_entries, (int)a.s_count,
                           a.ph_code, a.ph_step, (const uint4 *)a.ph_crit, a.ph_vslot};
-    hipLaunchKernelGGL((k_phase<N, TPL>), dim3(patches), dim3(PH_NT), 0, st, base, a.nW, pa, a.Wxy, a.power,
+    if (a.ph_entries > ph_entries_max<N>()) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_phase<N, TPL>), dim3(a.bt.patches), dim3(PH_NT), 0, st, a.nW, pa, a.Wxy, a.power,
                        a.mean_spec, a.bispec, a.bt, a.floor, a.noise_bias, a.amp, a.phasor);
     return hipGetLastError();
 }
 
-template <int N>
-hipError_t launch_phase_n(const SolveArgs &a, int base, int patches, hipStream_t st) {
-    if (a.ph_entries > ph_entries_max<N>()) return hipErrorInvalidValue;
-    switch (a.ph_tpl) {
-    case 2: return launch_phase_t<N, 2>(a, base, patches, st);
-    case 3: return launch_phase_t<N, 3>(a, base, patches, st);
-    case 4: return launch_phase_t<N, 4>(a, base, patches, st);
-    case 5: return launch_phase_t<N, 5>(a, base, patches, st);
-    case 6: return launch_phase_t<N, 6>(a, base, patches, st);
-    case 7: return launch_phase_t<N, 7>(a, base, patches, st);
-    }
-    return hipErrorInvalidValue;
-}
-
 template <int N, int TPL, int BIG>
-hipError_t launch_solve_t(const SolveArgs &a, int base, int patches, hipStream_t st) {
-    hipLaunchKernelGGL((k_solve<N, TPL, BIG>), dim3(patches), dim3(NT), 0, st, base, a.nW, a.n_units, a.units,
+hipError_t launch_solve_t(const SolveArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL((k_solve<N, TPL, BIG>), dim3(a.bt.patches), dim3(NT), 0, st, a.nW, a.n_units, a.units,
                        a.zero_slot, a.code, a.Wxy, a.power, a.mean_spec, a.bispec,
                        a.s_count, a.bt, a.floor, a.noise_bias, a.amp, a.phasor);
     return hipGetLastError();
 }
 
 template <int N, int BIG>
-hipError_t launch_solve_n(const SolveArgs &a, int base, int patches, hipStream_t st) {
+hipError_t launch_solve_n(const SolveArgs &a, hipStream_t st) {
     switch (solve_samples_per_lane(a.max_sw)) {
-    case 2: return launch_solve_t<N, 2, BIG>(a, base, patches, st);
-    case 4: return launch_solve_t<N, 4, BIG>(a, base, patches, st);
-    default: return launch_solve_t<N, 8, BIG>(a, base, patches, st);
+    case 2: return launch_solve_t<N, 2, BIG>(a, st);
+    case 4: return launch_solve_t<N, 4, BIG>(a, st);
+    default: return launch_solve_t<N, 8, BIG>(a, st);
     }
 }
-
-// Bursts of at most this many patches are solved by k_phase.  k_phase holds
-// one workgroup per CU at N = 128 and k_solve three, so k_phase wins while
-// the patches fit the 256 CUs at once (ms, N = 128, R = 10: 1 patch 0.54
-// against 0.76, 225 patches 0.63 against 0.85; R = 12: 256 patches 0.75
-// against 0.87) and not in a second round (300 patches: 1.16 against 1.14 at
-// R = 10, 1.42 against 1.21 at R = 12; 1287: 4.3 against 3.8).  The two
-// round differently, so the choice goes by the burst's own patches: a burst
-// gives the same phasors alone and in a batch.
-constexpr int PHASE_MAX_PATCHES = 256;
 
 }  // namespace
 
@@ -1067,21 +1041,13 @@ hipError_t launch_solve(const SolveArgs &a, hipStream_t st) {
     if (a.s_count * (int64_t)sizeof(float2) > INT32_MAX) return hipErrorInvalidValue;   // buffer range of B
     const bool small = a.n_inner <= Win<0>::INNER && a.ring <= Win<0>::RING;
     if (!small && (a.n_inner > Win<1>::INNER || a.ring > Win<1>::RING)) return hipErrorInvalidValue;
-    // runs of bursts of one kind
-    auto end_of = [&](int b) { return b + 1 < a.bt.nb ? a.bt.b[b + 1].patch0 : a.bt.patches; };
-    auto steps = [&](int b) { return a.ph_steps > 0 && end_of(b) - a.bt.b[b].patch0 <= PHASE_MAX_PATCHES; };
-    hipError_t e = hipSuccess;
-    for (int b = 0; b < a.bt.nb && e == hipSuccess;) {
-        const int base = a.bt.b[b].patch0;
-        const bool ph = steps(b);
-        while (b + 1 < a.bt.nb && steps(b + 1) == ph) ++b;
-        const int n = end_of(b++) - base;
-        if (n == 0) continue;
-        if (ph) e = a.N == 128 ? launch_phase_n<128>(a, base, n, st) : launch_phase_n<64>(a, base, n, st);
-        else if (a.N == 128) e = small ? launch_solve_n<128, 0>(a, base, n, st) : launch_solve_n<128, 1>(a, base, n, st);
-        else e = small ? launch_solve_n<64, 0>(a, base, n, st) : launch_solve_n<64, 1>(a, base, n, st);
+    if (a.ph_steps > 0) {                            // (the planner's choice: solve_in_steps)
+        if (a.N == 128 && a.ph_tpl == 5) return launch_phase_t<128, 5>(a, st);
+        if (a.N == 64 && a.ph_tpl == 2) return launch_phase_t<64, 2>(a, st);
+        return hipErrorInvalidValue;
     }
-    return e;
+    if (a.N == 128) return small ? launch_solve_n<128, 0>(a, st) : launch_solve_n<128, 1>(a, st);
+    return small ? launch_solve_n<64, 0>(a, st) : launch_solve_n<64, 1>(a, st);
 }
 
 }  // namespace nvsm

@@ -170,7 +170,7 @@ struct SolveArgs {
     int noise_bias = 0;
     double *amp = nullptr;
     double2 *phasor = nullptr;
-    // step schedule of k_phase (plan.hpp, PhaseSteps); 0 steps: k_solve
+    // step schedule of k_phase (plan.hpp, PhaseSteps and solve_in_steps); 0 steps: k_solve
     int ph_steps = 0, ph_tpl = 0, ph_early = 0, ph_entries = 0;
     const unsigned *ph_code = nullptr, *ph_step = nullptr, *ph_crit = nullptr;
     const int *ph_vslot = nullptr;

@@ -293,6 +293,29 @@ void plan_phase_steps(HostPlan *pl) {
         }
 }
 
+// The two kernels round differently and a burst gives the same phasors alone
+// and in any batch, so the choice can go neither by a burst's patches nor by
+// the batch's: k_phase is taken where it is not slower for any number of
+// them.  Its time over k_solve's, 1 to 2600 patches:
+//  * N = 64, two pairs per lane (R <= 6; three workgroups per CU): 0.58 to 0.83
+//    (R = 6: 93 us against 127 for one patch, 589 against 817 for 2600); with
+//    three (R = 7) up to 1.12, with four or five 1.28;
+//  * N = 128 holds one workgroup per CU, so k_phase, ahead up to 256 patches
+//    (0.60 to 0.86), needs a second round where k_solve does not: up to 1.47
+//    for R <= 9 (two samples per lane there), 1.18 for R = 12.  R = 10 pays for
+//    256 samples per w in k_solve and for 5 pairs of 32 lanes here: level past
+//    256 patches with u_cut >= 60 (0.98 to 1.03; one patch 0.53 against 0.75
+//    ms, 2600 patches 6.41 against 6.28), 1.06 at 48, 1.2 at 30;
+//  * where u_cut is close to R many w have more than PH_FRESH fresh samples
+//    and empty steps are put in: more than a tenth of the units, and k_phase
+//    falls behind (u_cut 12, R 10: 77 steps, 57 units, 38 us against 28).
+bool solve_in_steps(const HostPlan &pl) {
+    const PhaseSteps &ph = pl.ph;
+    if (ph.steps == 0 || 10 * ph.steps > 11 * pl.n_units) return false;
+    if (pl.N == 64) return ph.tpl == 2;
+    return ph.tpl == 5 && solve_samples_per_lane(pl.max_sw) == 4 && pl.uc >= 60;
+}
+
 bool build_plan(int N, int uc, int R, int K, HostPlan *pl, std::string *err) {
     if (K < 8 || K > BS_MAX_SLOTS || K % 8) { *err = "slots per wave must be 8..32, a multiple of 8"; return false; }
     pl->slots = K;

@@ -173,8 +173,9 @@ struct HostPlan {
     std::vector<float> filt;            // |W|: diffraction OTF at |w|/(N/2)
     double hann_sum2 = 0;               // sum of the 2-D taper
 
-    // Step schedule of the phase recursion (k_phase), for v radii of at most
-    // PH_MAX_PAIRS pairs +-v (R <= 12); ph.steps == 0 otherwise.
+    // Step schedule of the phase recursion (k_phase, where solve_in_steps), for
+    // v radii of at most PH_MAX_PAIRS pairs +-v (R <= 12); ph.steps == 0
+    // otherwise.
     PhaseSteps ph;
     LsqPairs lsq;
 };
@@ -193,6 +194,9 @@ void plan_lsq_pairs(HostPlan *pl);
 
 // The step schedule (ph) for the groups in group_wb, N, uc and R.
 void plan_phase_steps(HostPlan *pl);
+
+// Whether the recursion runs in those steps (k_phase) or in units (k_solve).
+bool solve_in_steps(const HostPlan &pl);
 
 // S in storage order, 4 ints per entry (wx, wy, vx, vy).
 void enumerate_S(int uc, int R, std::vector<int32_t> *wv);
