@@ -301,11 +301,12 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
 }
 
 // The passes over a patch's frame-group partials (below) give every entry of
-// the stored half plane (rows 0..N/2) a thread of its own, PARTS
-// workgroups per patch: each thread waits for its few dependent sums once, and
-// even one patch spreads over several CUs.  (One workgroup per patch walked
-// the whole plane in a chain of 64 waits: 74 us for 12 patches of 6 groups, 5 now;
-// 194 us for 1287 patches of 5 groups, 104 now.)  The
+// the stored half plane (rows 0..N/2) a thread of its own, PARTS workgroups per
+// patch (x the patch, y the part: both in x pass a grid's 2^32 threads at 1.86
+// million patches of 64 x 64, which memory holds): each thread waits for its few
+// dependent sums once, and even one patch spreads over several CUs.  (One
+// workgroup per patch walked the whole plane in a chain of 64 waits: 74 us for 12
+// patches of 6 groups, 5 now; 194 us for 1287 patches of 5 groups, 104 now.)  The
 // half plane's entry also writes its mirror, P(-u) = P(u).
 template <int N> struct FinGeom {
     static constexpr int NP = (N / 2 + 1) * N;               // stored entries
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int ch
                                                      float *__restrict__ power, float *__restrict__ mean_spec,
                                                      float *__restrict__ mu) {
     constexpr int NP = FinGeom<N>::NP;
-    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
+    const int patch = blockIdx.x, part = blockIdx.y;
     const int b = burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; });
     const BurstDesc &bd = bt.b[b];
     const int nchunks = (bd.F + chunk_frames - 1) / chunk_frames;
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(NT) void k_acc_stream(int F, int chunk_frames, cons
                                                    float inv_total, float *__restrict__ power,
                                                    float *__restrict__ mean_spec, float *__restrict__ mu) {
     constexpr int NP = FinGeom<N>::NP;
-    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
+    const int patch = blockIdx.x, part = blockIdx.y;
     const int nchunks = (F + chunk_frames - 1) / chunk_frames;
     const Partials<N, FINE> pt = {ppart, mpart, mupart, spectra, (size_t)patch * nchunks, (size_t)patch * F,
                                   chunk_frames, F};
@@ -482,7 +483,7 @@ hipError_t launch_ingest_f(const IngestArgs &a, hipStream_t st) {
     };
     const hipError_t e = a.vec ? ingest(k_ingest<N, T, true, FINE>) : ingest(k_ingest<N, T, false, FINE>);
     if (e != hipSuccess) return e;
-    const dim3 grid(a.bt.patches * FinGeom<N>::PARTS);
+    const dim3 grid(a.bt.patches, FinGeom<N>::PARTS);
     if (a.stream_mode == 0)
         hipLaunchKernelGGL((k_acc_finalize<N, FINE>), grid, dim3(NT), 0, st, a.bt, a.chunk_frames, a.ppart, a.mpart,
                            a.mupart, a.spectra, a.power, a.mean_spec, a.mu);
@@ -668,7 +669,7 @@ __global__ __launch_bounds__(NT) void k_noise_finalize(const BurstTable bt, int 
                                                        float2 *__restrict__ cgrid, float *__restrict__ nbar) {
     constexpr int NP = FinGeom<N>::NP;
     constexpr int FS = SpecRows<N>::FS;
-    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
+    const int patch = blockIdx.x, part = blockIdx.y;
     const int b = burst_of(bt, patch, [](const BurstDesc &d) { return (int64_t)d.patch0; });
     const BurstDesc &bd = bt.b[b];
     const int nchunks = (bd.F + chunk_frames - 1) / chunk_frames;
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(NT) void k_noise_stream(const BurstTable bt, int ch
                                                      float2 *__restrict__ cgrid, float *__restrict__ nbar) {
     constexpr int NP = FinGeom<N>::NP;
     constexpr int FS = SpecRows<N>::FS;
-    const int patch = blockIdx.x / FinGeom<N>::PARTS, part = blockIdx.x % FinGeom<N>::PARTS;
+    const int patch = blockIdx.x, part = blockIdx.y;
     const BurstDesc &bd = bt.b[0];
     const int nchunks = (bd.F + chunk_frames - 1) / chunk_frames;
     const size_t wg0 = (size_t)bd.ingest0 + (size_t)patch * nchunks;
@@ -777,10 +778,10 @@ hipError_t launch_noise_t(const NoiseArgs &na, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.stream_mode == 0)
-        hipLaunchKernelGGL((k_noise_finalize<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
+        hipLaunchKernelGGL((k_noise_finalize<N>), dim3(a.bt.patches, FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
                            na.spart, a.power, na.cgrid, na.nbar);
     else
-        hipLaunchKernelGGL((k_noise_stream<N>), dim3(a.bt.patches * FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
+        hipLaunchKernelGGL((k_noise_stream<N>), dim3(a.bt.patches, FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
                            na.spart, a.stream_mode, a.stream_first, a.inv_total, na.csc, na.ssc, a.power, na.cgrid,
                            na.nbar);
     return hipGetLastError();
