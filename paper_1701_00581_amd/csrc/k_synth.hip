@@ -4,13 +4,10 @@
 // filter(w) |O(w)| e(w) on W in LDS and inverts it with the forward FFT:
 // Re IFFT(X) = Re FFT(conj X) / N^2.  The mean level removed at ingest is
 // put back under the taper.
-// k_mosaic: the output pixels of the bursts of the launch, a row of one image
-// per workgroup row: each thread gathers, for its pixels, the subimages
+// k_mosaic: each thread gathers, for its pixels of one image, the subimages
 // covering them, out = sum r_k / sum taper_k (0 where < 1e-3).
 #include "device_common.hpp"
 #include "kernels.hpp"
-
-#include <algorithm>
 
 namespace nvsm {
 
@@ -61,23 +58,23 @@ __global__ __launch_bounds__(synth_threads<N>()) void k_synth(int nW, const int 
     }
 }
 
-// PX pixels per thread, x = PX (blockIdx.x NT + thread) + 0 .. PX - 1 of image
-// row blockIdx.z ROWS + blockIdx.y (over the bursts of the launch).  PX = 4 needs tile origins
-// and sizes in x that are multiples of 4: the four pixels then lie in the
-// same subimages and are loaded as one vector, and the row and tile arithmetic
-// is done once for four (58 us for 2560 x 2160 with one pixel and a 64-bit
-// division per thread, 26 now).
-constexpr int ROWS = 32768;                  // rows per grid plane (a grid's y extent is limited)
+// PX pixels per thread, x .. x + PX - 1 of one image row, the threads of an
+// image in row order over workgroups of its own (BurstDesc::mosaic0), so that
+// images of any width, alone and beside others, leave no lanes idle.  PX = 4
+// needs tile origins and sizes in x that are multiples of 4: the four pixels
+// then lie in the same subimages and are loaded as one vector, and the row and
+// tile arithmetic is done once for four (2560 x 2160: 58 us with one pixel and a
+// 64-bit division per thread, 26 now.  A workgroup per row of the launch's
+// widest image took 26 as well there, but 4.6 ms instead of 0.07 for fifteen
+// images 64 pixels wide beside one of 16384).
 template <int PX>
 __global__ __launch_bounds__(NT) void k_mosaic(const BurstTable bt, const float *__restrict__ all_patches, int N,
                                                int stride, int window, const float *__restrict__ hann) {
-    int b = 0, y = blockIdx.z * ROWS + blockIdx.y;
-    while (b + 1 < bt.nb && y >= bt.b[b].H) y -= bt.b[b++].H;
-    const BurstDesc &bd = bt.b[b];
-    if (y >= bd.H) return;
+    const BurstDesc &bd = bt.b[burst_of(bt, blockIdx.x, [](const BurstDesc &d) { return (int64_t)d.mosaic0; })];
     const int H = bd.H, W = bd.W, ny = bd.ny, nx = bd.nx;
-    const int x = PX * (blockIdx.x * NT + threadIdx.x);
-    if (x >= W) return;
+    const unsigned t = (blockIdx.x - bd.mosaic0) * NT + threadIdx.x, row = (unsigned)W / PX;   // (t < H W + NT < 2^32)
+    const int y = (int)(t / row), x = (int)(t % row) * PX;
+    if (y >= H) return;
     const float *patches = all_patches + (size_t)bd.patch0 * N * N;
     float num[PX], dx[PX], dy = 0.f;
 #pragma unroll
@@ -124,23 +121,22 @@ hipError_t launch_synth_t(const SynthArgs &a, hipStream_t st) {
     hipLaunchKernelGGL(k_synth<N>, dim3(a.bt.patches), dim3(synth_threads<N>()), 0, st, a.nW, a.Wxy, a.amp, a.phasor, a.filt,
                        a.mu, a.window, a.hann, a.twiddle, a.patch_buf);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !a.mosaic || a.bt.pixels == 0) return e;
-    // rows of all images, and the widest; four pixels per thread where every
-    // tile starts and every image ends at a multiple of 4 (and the subimages
-    // are aligned for it)
-    int rows = 0, widest = 0;
+    if (e != hipSuccess || !a.mosaic) return e;
+    // four pixels per thread where every tile starts and every image ends at a
+    // multiple of 4 (and the subimages are aligned for it)
+    BurstTable bt = a.bt;
     bool quad = a.stride % 4 == 0 && (uintptr_t)a.patch_buf % 16 == 0;
-    for (int i = 0; i < a.bt.nb; ++i) {
-        rows += a.bt.b[i].H;
-        widest = std::max(widest, a.bt.b[i].W);
-        quad = quad && a.bt.b[i].W % 4 == 0;
+    for (int i = 0; i < bt.nb; ++i) quad = quad && bt.b[i].W % 4 == 0;
+    int wgs = 0;
+    for (int i = 0; i < bt.nb; ++i) {
+        bt.b[i].mosaic0 = wgs;
+        wgs += (int)(((int64_t)bt.b[i].H * bt.b[i].W / (quad ? 4 : 1) + NT - 1) / NT);
     }
-    const int px = quad ? 4 : 1;
-    const dim3 grid((widest + px * NT - 1) / (px * NT), std::min(rows, ROWS), (rows + ROWS - 1) / ROWS);
+    const dim3 grid(wgs);
     if (quad)
-        hipLaunchKernelGGL(k_mosaic<4>, grid, dim3(NT), 0, st, a.bt, a.patch_buf, N, a.stride, a.window, a.hann);
+        hipLaunchKernelGGL(k_mosaic<4>, grid, dim3(NT), 0, st, bt, a.patch_buf, N, a.stride, a.window, a.hann);
     else
-        hipLaunchKernelGGL(k_mosaic<1>, grid, dim3(NT), 0, st, a.bt, a.patch_buf, N, a.stride, a.window, a.hann);
+        hipLaunchKernelGGL(k_mosaic<1>, grid, dim3(NT), 0, st, bt, a.patch_buf, N, a.stride, a.window, a.hann);
     return hipGetLastError();
 }
 

@@ -9,25 +9,24 @@ namespace nvsm {
 // One burst of a launch.  A launch covers up to MAX_BURSTS bursts that
 // share the patch size and index sets; their patches are numbered
 // consecutively (patch0), as are their ingest workgroups (ingest0), stored
-// spectrum records (spec0, in records of one patch and frame) and output
-// pixels (pix0).  The table travels by value in the kernel arguments.
+// spectrum records (spec0, in records of one patch and frame) and, within
+// the mosaic's launch, its workgroups (mosaic0).  The table travels by value
+// in the kernel arguments.
 constexpr int MAX_BURSTS = 16;
 struct BurstDesc {
     const void *frames = nullptr;         // [F][H][pitch] pixels
     int64_t pitch = 0;                    // pixels per row
     int64_t spec0 = 0;                    // first stored spectrum record
-    int64_t pix0 = 0;                     // first output pixel (mosaic)
     const double *stf = nullptr;          // [N][N]
     float *out = nullptr;                 // [H][W]
     int F = 0, H = 0, W = 0, ny = 0, nx = 0;
-    int patch0 = 0, ingest0 = 0, pad = 0;
+    int patch0 = 0, ingest0 = 0, mosaic0 = 0;
 };
 struct BurstTable {
     int nb = 0;
     int patches = 0;                      // total over the bursts
     int ingest_wgs = 0;                   // total ingest workgroups
     int pad = 0;
-    int64_t pixels = 0;                   // total output pixels
     BurstDesc b[MAX_BURSTS];
 };
 

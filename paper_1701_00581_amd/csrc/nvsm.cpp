@@ -129,28 +129,26 @@ struct BurstIn {
     float *out = nullptr;
 };
 
-// Numbers the patches, ingest workgroups, spectrum records and output
-// pixels of up to MAX_BURSTS bursts consecutively.
+// Numbers the patches, ingest workgroups and spectrum records of up to
+// MAX_BURSTS bursts consecutively.
 void make_table(const nvsm_params *p, const BurstIn *in, int n, BurstTable *bt, int64_t *records) {
     *bt = BurstTable();
     bt->nb = n;
-    int64_t P = 0, wgs = 0, rec = 0, pix = 0;
+    int64_t P = 0, wgs = 0, rec = 0;
     for (int i = 0; i < n; ++i) {
         Tiling t;
         make_tiling(in[i].H, in[i].W, p->patch, p->stride, &t);
         BurstDesc &d = bt->b[i];
         d.frames = in[i].frames; d.pitch = in[i].pitch; d.stf = in[i].stf; d.out = in[i].out;
         d.F = in[i].F; d.H = in[i].H; d.W = in[i].W; d.ny = t.ny; d.nx = t.nx;
-        d.patch0 = (int)P; d.ingest0 = (int)wgs; d.spec0 = rec; d.pix0 = pix;
+        d.patch0 = (int)P; d.ingest0 = (int)wgs; d.spec0 = rec;
         const int64_t Pb = (int64_t)t.ny * t.nx;
         P += Pb;
         wgs += Pb * ((in[i].F + CHUNK_FRAMES - 1) / CHUNK_FRAMES);
         rec += Pb * in[i].F;
-        pix += (int64_t)in[i].H * in[i].W;
     }
     bt->patches = (int)P;
     bt->ingest_wgs = (int)wgs;
-    bt->pixels = pix;
     *records = rec;
 }
 
