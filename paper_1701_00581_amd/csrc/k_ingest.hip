@@ -300,17 +300,22 @@ __global__ __launch_bounds__(ingest_threads<T>()) void k_ingest(const BurstTable
     if (tid == 0) mupart[L] = mus - muc;
 }
 
-// The passes over a patch's frame-group partials (below) give every entry of
-// the stored half plane (rows 0..N/2) a thread of its own, PARTS workgroups per
+// The passes over a patch's frame-group partials (below) spread the stored half
+// plane's entries (rows 0..N/2) over the threads of parts(patches) workgroups per
 // patch (x the patch, y the part: both in x pass a grid's 2^32 threads at 1.86
-// million patches of 64 x 64, which memory holds): each thread waits for its few
-// dependent sums once, and even one patch spreads over several CUs.  (One
-// workgroup per patch walked the whole plane in a chain of 64 waits: 74 us for 12
-// patches of 6 groups, 5 now; 194 us for 1287 patches of 5 groups, 104 now.)  The
-// half plane's entry also writes its mirror, P(-u) = P(u).
+// million patches of 64 x 64, which memory holds).  Few patches: an entry a
+// thread, so that each waits for its few dependent sums once and even one patch
+// spreads over several CUs (one workgroup per patch: 74 us for 12 patches of 6
+// groups, 5 now).  Many: three workgroups, as a workgroup of one entry a thread
+// costs more to start than it reads (N = 64, one group: 10000 patches 73 us
+// with one workgroup in a chain of waits, 81 with an entry a thread, 66 with
+// three workgroups; 1296 patches of 5 groups: N = 64 47, 33 and 32, N = 128
+// 180, 103 and 101).  The half plane's entry also writes its
+// mirror, P(-u) = P(u).
 template <int N> struct FinGeom {
     static constexpr int NP = (N / 2 + 1) * N;               // stored entries
-    static constexpr int PARTS = (NP + NT - 1) / NT;         // workgroups per patch
+    static constexpr int PARTS = (NP + NT - 1) / NT;         // workgroups per patch at an entry a thread
+    static int parts(int patches) { return std::min(PARTS, std::max(3, 4096 / patches + 1)); }
 };
 
 // Index of -u for entry j of the half plane, or -1 where no row above N/2
@@ -388,8 +393,7 @@ __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int ch
     const Partials<N, FINE> pt = {ppart, mpart, mupart, spectra,
                                   (size_t)bd.ingest0 + (size_t)(patch - bd.patch0) * nchunks,
                                   (size_t)bd.spec0 + (size_t)(patch - bd.patch0) * bd.F, chunk_frames, bd.F};
-    const int j = part * NT + threadIdx.x;
-    if (j < NP) {
+    for (int j = part * NT + threadIdx.x; j < NP; j += gridDim.y * NT) {
         float s = 0.f, c = 0.f;
 #pragma unroll FINE ? 1 : 8
         for (int k = 0; k < nchunks; ++k) kahan_add(s, c, pt.power(k, j));
@@ -399,7 +403,7 @@ __global__ __launch_bounds__(NT) void k_acc_finalize(const BurstTable bt, int ch
         const int m = mirror_of<N>(j);
         if (m >= 0) pw[m] = v;
     }
-    if (part != FinGeom<N>::PARTS - 1) return;   // (the part with the fewest entries)
+    if (part != (int)gridDim.y - 1) return;
     const int i = threadIdx.x - (NT - 5);
     if (i >= 0 && i < 4) {
         float s = 0.f, c = 0.f;
@@ -432,8 +436,7 @@ __global__ __launch_bounds__(NT) void k_acc_stream(int F, int chunk_frames, cons
     const int nchunks = (F + chunk_frames - 1) / chunk_frames;
     const Partials<N, FINE> pt = {ppart, mpart, mupart, spectra, (size_t)patch * nchunks, (size_t)patch * F,
                                   chunk_frames, F};
-    const int j = part * NT + threadIdx.x;
-    if (j < NP) {
+    for (int j = part * NT + threadIdx.x; j < NP; j += gridDim.y * NT) {
         float2 *ps = psc + (size_t)patch * NP + j;
         float2 v = first ? make_float2(0.f, 0.f) : *ps;
 #pragma unroll FINE ? 1 : 8
@@ -447,7 +450,7 @@ __global__ __launch_bounds__(NT) void k_acc_stream(int F, int chunk_frames, cons
             if (mj >= 0) pw[mj] = m;
         }
     }
-    if (part != FinGeom<N>::PARTS - 1) return;
+    if (part != (int)gridDim.y - 1) return;
     const int i = threadIdx.x - (NT - 5);
     if (i >= 0 && i < 4) {
         const size_t o = (size_t)patch * 4 + i;
@@ -483,7 +486,7 @@ hipError_t launch_ingest_f(const IngestArgs &a, hipStream_t st) {
     };
     const hipError_t e = a.vec ? ingest(k_ingest<N, T, true, FINE>) : ingest(k_ingest<N, T, false, FINE>);
     if (e != hipSuccess) return e;
-    const dim3 grid(a.bt.patches, FinGeom<N>::PARTS);
+    const dim3 grid(a.bt.patches, FinGeom<N>::parts(a.bt.patches));
     if (a.stream_mode == 0)
         hipLaunchKernelGGL((k_acc_finalize<N, FINE>), grid, dim3(NT), 0, st, a.bt, a.chunk_frames, a.ppart, a.mpart,
                            a.mupart, a.spectra, a.power, a.mean_spec, a.mu);
@@ -687,17 +690,18 @@ __global__ __launch_bounds__(NT) void k_noise_finalize(const BurstTable bt, int 
         nbar[(size_t)patch * 2] = q0;
         nbar[(size_t)patch * 2 + 1] = t3;
     }
-    const int j = part * NT + threadIdx.x;
-    if (j >= NP) return;
-    const float2 *cp = cpart + wg0 * NP + j;
-    float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
+    for (int j = part * NT + threadIdx.x; j < NP; j += gridDim.y * NT) {
+        const float2 *cp = cpart + wg0 * NP + j;
+        float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
 #pragma unroll 8
-    for (int k = 0; k < nchunks; ++k) {
-        const float2 v = cp[(size_t)k * NP];
-        kahan_add(sx, cx, v.x);
-        kahan_add(sy, cy, v.y);
+        for (int k = 0; k < nchunks; ++k) {
+            const float2 v = cp[(size_t)k * NP];
+            kahan_add(sx, cx, v.x);
+            kahan_add(sy, cy, v.y);
+        }
+        noise_store<N>(j, (sx - cx) * invF, (sy - cy) * invF, q0, cgrid + (size_t)patch * FS,
+                       power + (size_t)patch * N * N);
     }
-    noise_store<N>(j, (sx - cx) * invF, (sy - cy) * invF, q0, cgrid + (size_t)patch * FS, power + (size_t)patch * N * N);
 }
 
 // The streaming form of k_noise_finalize: adds the group's sums (its frame
@@ -742,26 +746,26 @@ __global__ __launch_bounds__(NT) void k_noise_stream(const BurstTable bt, int ch
             }
         }
     }
-    const int j = part * NT + threadIdx.x;
-    if (j >= NP) return;
-    const float2 *cp = cpart + wg0 * NP + j;
-    float4 *cs = csc + (size_t)patch * NP + j;
-    float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
-    if (!first) {
-        const float4 r = *cs;
-        sx = r.x; sy = r.y; cx = r.z; cy = r.w;
-    }
+    for (int j = part * NT + threadIdx.x; j < NP; j += gridDim.y * NT) {
+        const float2 *cp = cpart + wg0 * NP + j;
+        float4 *cs = csc + (size_t)patch * NP + j;
+        float sx = 0.f, cx = 0.f, sy = 0.f, cy = 0.f;
+        if (!first) {
+            const float4 r = *cs;
+            sx = r.x; sy = r.y; cx = r.z; cy = r.w;
+        }
 #pragma unroll 8
-    for (int k = 0; k < nchunks; ++k) {
-        const float2 v = cp[(size_t)k * NP];
-        kahan_add(sx, cx, v.x);
-        kahan_add(sy, cy, v.y);
+        for (int k = 0; k < nchunks; ++k) {
+            const float2 v = cp[(size_t)k * NP];
+            kahan_add(sx, cx, v.x);
+            kahan_add(sy, cy, v.y);
+        }
+        if (mode == 1)
+            *cs = make_float4(sx, sy, cx, cy);
+        else
+            noise_store<N>(j, (sx - cx) * inv_total, (sy - cy) * inv_total, q0, cgrid + (size_t)patch * FS,
+                           power + (size_t)patch * N * N);
     }
-    if (mode == 1)
-        *cs = make_float4(sx, sy, cx, cy);
-    else
-        noise_store<N>(j, (sx - cx) * inv_total, (sy - cy) * inv_total, q0, cgrid + (size_t)patch * FS,
-                       power + (size_t)patch * N * N);
 }
 
 template <int N, typename T>
@@ -778,10 +782,12 @@ hipError_t launch_noise_t(const NoiseArgs &na, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.stream_mode == 0)
-        hipLaunchKernelGGL((k_noise_finalize<N>), dim3(a.bt.patches, FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
+        hipLaunchKernelGGL((k_noise_finalize<N>), dim3(a.bt.patches, FinGeom<N>::parts(a.bt.patches)), dim3(NT), 0, st, a.bt,
+                           a.chunk_frames, na.cpart,
                            na.spart, a.power, na.cgrid, na.nbar);
     else
-        hipLaunchKernelGGL((k_noise_stream<N>), dim3(a.bt.patches, FinGeom<N>::PARTS), dim3(NT), 0, st, a.bt, a.chunk_frames, na.cpart,
+        hipLaunchKernelGGL((k_noise_stream<N>), dim3(a.bt.patches, FinGeom<N>::parts(a.bt.patches)), dim3(NT), 0, st, a.bt,
+                           a.chunk_frames, na.cpart,
                            na.spart, a.stream_mode, a.stream_first, a.inv_total, na.csc, na.ssc, a.power, na.cgrid,
                            na.nbar);
     return hipGetLastError();

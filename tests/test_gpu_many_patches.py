@@ -41,3 +41,27 @@ def test_every_patch_of_a_very_large_burst_is_written(noise_bias):
     nv.nvsm_destroy(ctx)
     del power, mean, mu
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N,dtype", [(64, "float32"), (128, "uint16")])
+def test_parts_of_a_patch_do_not_change_its_sums(N, dtype):
+    """The passes over the frame groups split a patch by the number of patches
+    (one entry a thread, fewer workgroups above 4096 / parts): a patch's power,
+    means and photon-noise terms are the same for 1, 36 and 2025 of them."""
+    import torch
+    import paper_1701_00581_amd as nv
+    F, stride = 23, N // 2
+    for noise_bias in (0, 2):
+        p = nv.default_params(N, v_radius=2, u_cut=4, noise_bias=noise_bias, photons_per_adu=2.0)
+        L = lambda side: N + (side - 1) * stride  # noqa: E731
+        g = torch.Generator(device="cuda").manual_seed(N)
+        fr = (100 + 3000 * torch.rand(F, L(45), L(45), device="cuda", generator=g)).to(getattr(torch, dtype))
+        ref = None
+        for side in (45, 6, 1):
+            s = nv.Session(p, L(side), L(side), F)
+            s.accumulate(fr[:, :L(side), :L(side)].contiguous())
+            rows = [y * side + x for y in range(min(side, 6)) for x in range(min(side, 6))]
+            got = [t[rows].clone() for t in (s.power, s.mean_spec, s.mu, s.bispec)]
+            s.close()
+            ref = ref or got
+            assert all(torch.equal(a[:len(rows)], b) for a, b in zip(ref, got))
