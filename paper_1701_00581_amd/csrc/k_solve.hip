@@ -408,8 +408,9 @@ __global__ __launch_bounds__(PH_NT) __attribute__((amdgpu_waves_per_eu(N == 128 
         const double2 s = unit_or_one(make_double2((double)m[0], (double)m[1]));
         ph_out[tid] = s;
         const uint4 c = pa.crit[tid];
-        e[c.x] = s;
-        e[c.y] = make_double2(s.x, -s.y);
+        const bool fin = fabs(s.x) + fabs(s.y) <= 2.0;
+        e[c.x] = fin ? s : make_double2(0.0, 0.0);
+        e[c.y] = fin ? make_double2(s.x, -s.y) : make_double2(0.0, 0.0);
     }
     __syncthreads();
 
@@ -469,7 +470,11 @@ __global__ __launch_bounds__(PH_NT) __attribute__((amdgpu_waves_per_eu(N == 128 
                     const double rn = rsqrt(n);
                     const bool some = n > 0.0;
                     v = make_double2(some ? zx * rn : 1.0, some ? zy * rn : 0.0);
-                    if ((int)c[d].z >= 0) e[c[d].z] = make_double2(v.x, (lane & 7) ? -v.y : v.y);
+                    // (a phasor that is not finite, of an overflowed sum, counts as 0
+                    // from here on: a bulk lane multiplies pairs without a sample too)
+                    const bool fin = n < __builtin_inf() || !some;
+                    if ((int)c[d].z >= 0)
+                        e[c[d].z] = make_double2(fin ? v.x : 0.0, fin ? ((lane & 7) ? -v.y : v.y) : 0.0);
                     out = (int)c[d].w;
                 }
             }
