@@ -501,11 +501,9 @@ template <int N, typename T>
 hipError_t launch_ingest_t(const IngestArgs &a, hipStream_t st) {
     // FINE needs room for its values in the partials of each frame's group,
     // and groups of whole pairs
-    if constexpr (N >= 64) {
-        static_assert(FinGeom<N>::NP >= FINE_MAX_FRAMES * fine_stride<N>(), "fine values fit the partials");
-        if (a.bt.ingest_wgs <= FINE_MAX_WGS && a.chunk_frames <= FINE_MAX_FRAMES && a.chunk_frames % 2 == 0)
-            return launch_ingest_f<N, T, true>(a, st);
-    }
+    static_assert(FinGeom<N>::NP >= FINE_MAX_FRAMES * fine_stride<N>(), "fine values fit the partials");
+    if (a.bt.ingest_wgs <= FINE_MAX_WGS && a.chunk_frames <= FINE_MAX_FRAMES && a.chunk_frames % 2 == 0)
+        return launch_ingest_f<N, T, true>(a, st);
     return launch_ingest_f<N, T, false>(a, st);
 }
 
