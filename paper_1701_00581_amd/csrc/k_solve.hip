@@ -280,17 +280,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(TPL <= 4 ? 6
     }
 }
 
-// n consecutive words at byte offset off of r (n 1..4)
+// n consecutive words at byte offset off of r (n 1, 2 or 4)
 template <int n>
 __device__ __forceinline__ void load_words(const __amdgpu_buffer_rsrc_t r, unsigned off, unsigned *w) {
+    static_assert(n == 1 || n == 2 || n == 4, "pairs +-v per lane: 2 or 5");
     if constexpr (n == 1) w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
     if constexpr (n == 2) {
         const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
         w[0] = v[0]; w[1] = v[1];
-    }
-    if constexpr (n == 3) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b96(r, (int)off, 0, 0);
-        w[0] = v[0]; w[1] = v[1]; w[2] = v[2];
     }
     if constexpr (n == 4) {
         const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
@@ -332,12 +329,13 @@ struct PhaseArgs {
 // one LDS gather, on a raster of the plane where neighbouring lanes read
 // neighbouring entries.  Codes are loaded RING - 1 steps ahead and the samples
 // they place AHEAD steps ahead.
-// The 1094 steps at N = 128, R = 10 take 0.49 us each: a vector load holds a
-// bulk wave for about 43 clocks, an LDS gather for 24, a sample's arithmetic
-// for 77, together about 1130 of a step's 1190 clocks.  Fewer, wider loads and
-// one sample's loads between the next samples' arithmetic took it from 0.57;
-// the memory's latency is not in it (the same with every load from one 4 KB
-// window).
+// The 1094 steps at N = 128, R = 10 take 0.49 us (about 1190 clocks) each.  Timing
+// variants put a vector load at about 43 clocks of a bulk wave, an LDS gather at
+// 24 and a sample's arithmetic at 77, together 1130 of them; the counters have the
+// waves issuing for 40 % of their time and waiting for 53 %.  Fewer, wider loads
+// and one sample's loads between the next samples' arithmetic took a step from
+// 0.57 us; the memory's latency is not in it (the same with every load from one
+// 4 KB window).
 // The raster (154 KB at N = 128) allows one workgroup per CU there, whose 8
 // waves then have 256 registers each; at N = 64 (45 KB, two pairs per lane in 76
 // registers) a CU holds three.  Waves past the bulk waves share the set-up and
@@ -809,9 +807,9 @@ __global__ __launch_bounds__(LSQ_NT) void k_lsq(int nW, int n_inner, int iters, 
 // array until the step ends (in registers they made the kernel spill).
 // k_lsq issues about 110 instructions a sample, this about 55.
 // 10 steps of 81 patches (N = 128, R = 10): 14.8 -> 7.4 ms (9.5 with 8 waves); the
-// phasors are 7e-14 from the FP64 ones (k_lsq 2.6e-13).  VALU issue is at 0.66
-// and the LDS pipe at 0.56 of the cycles, three quarters of that conflicts of
-// the gathers and adds, whose entries lie in order of |w|.
+// phasors are 7e-14 from the FP64 ones (k_lsq 2.6e-13).  On the 81 CUs in use VALU
+// issue is at 0.66 and the LDS pipe at 0.53 of the cycles, three quarters of that
+// conflicts of the gathers and adds, whose entries lie in order of |w|.
 constexpr int LQ_NT = 1024, LQ_NWAVE = LQ_NT / 64, LQ_SLOTS = (LSQ_MAXW + LQ_NT - 1) / LQ_NT;
 template <int TPL>
 __global__ __launch_bounds__(LQ_NT) void k_lsq_pairs(int nW, int n_inner, int iters, const int *__restrict__ woff,
