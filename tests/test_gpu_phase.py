@@ -1,6 +1,7 @@
-"""The phase recursion in steps (k_phase) against the FP64 oracle, at the edges
-of its range: 1 to 4 pairs +-v per lane, exactly full lanes and remainders, the
-smallest W, and a mean bispectrum that is zero for some w."""
+"""The phase recursion against the FP64 oracle at the edges of the step
+schedule's range: radii of 2 to 7 pairs +-v per lane, exactly full lanes and
+remainders, the smallest W, and a mean bispectrum that is zero for some w
+(solve_in_steps says which of these run in steps and which in units)."""
 import numpy as np
 import pytest
 
@@ -60,9 +61,8 @@ def test_phase_steps_against_the_oracle(N, u_cut, R):
 
 
 def test_batch_of_both_kinds_equals_alone():
-    """A batch whose bursts lie on both sides of the patch count (256) that
-    separates the two phase kernels: each burst's phasors are those of the
-    same burst alone, bit for bit."""
+    """A batch whose bursts hold fewer and more patches than the card has CUs
+    (256): each burst's image is that of the same burst alone, bit for bit."""
     import torch
     import paper_1701_00581_amd as nv
     p = nv.default_params(64, v_radius=4, stride=32)
@@ -88,7 +88,7 @@ def test_batch_of_both_kinds_equals_alone():
 @pytest.mark.parametrize("N,u_cut,R,spike", [(128, 63, 12, 1), (128, 40, 9, 1), (64, 31, 8, 1e7), (64, 20, 12, 1e3),
                                              (64, 5, 4, 1), (64, 2, 1, 1)])
 def test_least_squares_pairs_against_the_oracle(N, u_cut, R, spike):
-    """The least-squares steps with pairs over the lanes (k_lsq_pairs): 1 to 4
+    """The least-squares steps with pairs over the lanes (k_lsq_pairs): 2 and 4
     pairs per lane, W shorter than a round, and a sample that outweighs the
     others (its adds take the full conversion)."""
     import torch

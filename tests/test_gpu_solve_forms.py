@@ -96,3 +96,30 @@ def test_order_of_a_batch_costs_nothing(R):
     assert min(times[1::2]) <= 1.5 * min(times[::2])
     assert all(torch.equal(a, b) for a, b in zip(images[0], images[1]))
     nv.nvsm_destroy(ctx)
+
+
+@pytest.mark.parametrize("N,u_cut,R", [(128, 63, 10), (64, 31, 9), (64, 31, 10), (64, 31, 11)])
+def test_least_squares_with_three_pairs_per_lane(N, u_cut, R):
+    """The least-squares steps at 2, 3 and 4 pairs per lane on either side of
+    each change, against the oracle."""
+    import torch
+    import paper_1701_00581_amd as nv
+    p = nv.default_params(N, u_cut=u_cut, v_radius=R, phase_method=1, lsq_iters=2)
+    Wset, S, woff = oracle.bispectrum_set(u_cut, R)
+    B, M = _inputs(np.random.default_rng(5 + N + R), N, Wset, S)
+    s = nv.Session(p, N, N, 1)
+    s.bispec.copy_(torch.from_numpy(B.view(np.float32).reshape(1, len(S), 2)))
+    s.mean_spec.copy_(torch.from_numpy(M.view(np.float32).reshape(1, 2, 2)))
+    s.power.fill_(1.0)
+    s.solve(torch.ones(N, N, dtype=torch.float64, device="cuda"))
+    e = s.phasor.cpu().numpy()[0]
+    s.close()
+    B64 = B.astype(np.complex128)
+    ref = oracle.phase_recursion(B64, M[0], M[1], Wset, S, woff, N)
+    ref = oracle.phase_least_squares(B64, ref, Wset, S, woff, 2)
+    rms, worst = phase_rms(e[..., 0] + 1j * e[..., 1], ref)
+    say(f"lsq N {N} R {R}: rms {rms:.1e} worst {worst:.1e}")
+    # as in the test of the pairs: adds off by half a unit of s1 2^-62, a few
+    # hundred to a sum of modulus at least 1, doubled by each of two steps
+    s1 = float(np.abs(B64.real).sum() + np.abs(B64.imag).sum())
+    assert worst <= 4 * (300 * s1 * 2.0 ** -62 + TOL)
