@@ -308,6 +308,7 @@ nvsm_status get_plan(nvsm_context *ctx, const nvsm_params *p, int slots, DeviceP
         return fail(ctx, NVSM_ERR_OOM, "host allocation failed while planning");
     }
     const HostPlan &h = dp->h;
+    if (!solve_in_steps(h)) dp->h.ph = PhaseSteps();   // (its tables are not used)
     dp->max_sw = h.max_sw;
     if (h.solve_code.empty() || h.n_inner > 512 || h.ring_size > 3072)
         return fail(ctx, NVSM_ERR_INVALID_ARG, "sample count or phasor window too large for the phase kernel");
@@ -457,7 +458,7 @@ hipError_t run_solve(nvsm_context *ctx, DevicePlan *dp, const nvsm_params *p, co
     a.power = power; a.mean_spec = mean_spec; a.bispec = (const float2 *)bispec; a.s_count = dp->h.s_count;
     a.floor = p->stf_floor; a.noise_bias = p->noise_bias == 1; a.amp = amp;
     a.phasor = (double2 *)phasor;
-    a.ph_steps = solve_in_steps(dp->h) ? dp->h.ph.steps : 0; a.ph_tpl = dp->h.ph.tpl; a.ph_early = dp->h.ph.early;
+    a.ph_steps = dp->h.ph.steps; a.ph_tpl = dp->h.ph.tpl; a.ph_early = dp->h.ph.early;
     a.ph_entries = dp->h.ph.entries;
     a.ph_code = dp->ph_code; a.ph_step = dp->ph_step; a.ph_crit = dp->ph_crit; a.ph_vslot = dp->ph_vslot;
     a.phase_method = p->phase_method; a.lsq_iters = p->lsq_iters;
